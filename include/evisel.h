@@ -209,8 +209,8 @@ evisel_status evisel_mask_export_pairs(const evisel_mask* mask, int32_t* a,
  *              video's query tokens of that coarse probability on the
  *              frame's visual tokens (the coarse counterpart of
  *              evisel_sparse_prefill's evidence slice)
- * The call runs the retention itself (as evisel_select_blocks, into the
- * workspace) and then the coarse pass; no attention output is formed.
+ * The call decides the retention itself, for the query tokens only (the
+ * rule of evisel_select_blocks); no attention output is formed.
  * Errors: INVALID_ARG (static or host-only mask, NULL or misaligned
  * pointer), UNSUPPORTED (d, dtype, B), WORKSPACE, HIP. */
 evisel_status evisel_coarse_evidence(const evisel_mask* mask, const void* q,

@@ -643,10 +643,9 @@ evisel_status evisel_coarse_evidence(const evisel_mask* m, const void* q,
   const evisel::Workspace w = carve(wl, workspace, true);
   const evisel::SelCall c = sel_call(q, k, d, dtype, softmax_scale,
                                      P.rule.tau, w.rbits, w.ubits);
-  hipStream_t s = (hipStream_t)stream;
-  hipError_t e = evisel::launch_select(m->dp, w, c, s);
-  if (e != hipSuccess) return hip_fail(e, "retention launch");
-  e = evisel::launch_coarse(m->dp, w, c, w.cpart, evidence, s);
+  const hipError_t e =
+      evisel::launch_coarse(m->dp, w, c, w.cpart, evidence,
+                            (hipStream_t)stream);
   if (e != hipSuccess) return hip_fail(e, "coarse evidence launch");
   return EVISEL_OK;
 }

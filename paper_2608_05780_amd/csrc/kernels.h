@@ -92,8 +92,8 @@ hipError_t launch_attention_pipe(const DevPlan& p, const Workspace& w,
 size_t select_lds_need(int nh_max, int W);
 hipError_t launch_select(const DevPlan& p, const Workspace& w,
                          const SelCall& c, hipStream_t s);
-// Coarse query-frame evidence of one layer (top-p masks; the retention
-// bits must already be in w.rbits): out [hq][T]. cpart holds
+// Coarse query-frame evidence of one layer (top-p masks; mean keys and the
+// query rows' retention included): out [hq][T]. cpart holds
 // coarse_part_floats() floats of per-block partial sums.
 size_t coarse_part_floats(int n_tiles, int hq, int W);
 hipError_t launch_coarse(const DevPlan& p, const Workspace& w,

@@ -91,7 +91,7 @@ __global__ __launch_bounds__(D) void pool_kernel(const DevPlan pl,
   }
 }
 
-// Reductions over the TPR lanes of a row (TPR = 4, 8 or 16 consecutive
+// Reductions over the TPR lanes of a row (TPR = 4, 8, 16 or 64 consecutive
 // lanes). Each step combines a lane with a partner that holds the same
 // partial as the lane's own mirror image, so every lane of the group ends
 // with the same bits (fp addition is commutative).
@@ -108,12 +108,26 @@ constexpr int kQuadSwap2 = 0x4E;      // quad_perm [2, 3, 0, 1]
 constexpr int kHalfMirror = 0x141;    // lane i <-> 7 - i within 8
 constexpr int kRowMirror = 0x140;     // lane i <-> 15 - i within 16
 
+// Lane l's value combined with lane l ^ 16's, then l ^ 32's (swaps of 16- and
+// 32-lane halves: both lanes of a pair see the same two operands).
+template <class F>
+__device__ __forceinline__ unsigned cross_rows(unsigned x, F op) {
+  const auto a = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+  x = op(a[0], a[1]);
+  const auto b = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+  return op(b[0], b[1]);
+}
+
 template <int TPR>
 __device__ __forceinline__ float grp_sum(float x) {
   x += dppf<kQuadSwap1>(x);
   x += dppf<kQuadSwap2>(x);
   if (TPR >= 8) x += dppf<kHalfMirror>(x);
   if (TPR >= 16) x += dppf<kRowMirror>(x);
+  if (TPR >= 64)
+    x = __uint_as_float(cross_rows(__float_as_uint(x), [](unsigned a, unsigned b) {
+      return __float_as_uint(__uint_as_float(a) + __uint_as_float(b));
+    }));
   return x;
 }
 template <int TPR>
@@ -122,6 +136,9 @@ __device__ __forceinline__ int grp_sumi(int x) {
   x += dpp<kQuadSwap2>(x);
   if (TPR >= 8) x += dpp<kHalfMirror>(x);
   if (TPR >= 16) x += dpp<kRowMirror>(x);
+  if (TPR >= 64)
+    x = (int)cross_rows((unsigned)x,
+                        [](unsigned a, unsigned b) { return a + b; });
   return x;
 }
 template <int TPR>
@@ -130,6 +147,10 @@ __device__ __forceinline__ float grp_max(float x) {
   x = fmaxf(x, dppf<kQuadSwap2>(x));
   if (TPR >= 8) x = fmaxf(x, dppf<kHalfMirror>(x));
   if (TPR >= 16) x = fmaxf(x, dppf<kRowMirror>(x));
+  if (TPR >= 64)
+    x = __uint_as_float(cross_rows(__float_as_uint(x), [](unsigned a, unsigned b) {
+      return __float_as_uint(fmaxf(__uint_as_float(a), __uint_as_float(b)));
+    }));
   return x;
 }
 template <int TPR>
@@ -138,6 +159,8 @@ __device__ __forceinline__ unsigned grp_minu(unsigned x) {
   x = min(x, (unsigned)dpp<kQuadSwap2>((int)x));
   if (TPR >= 8) x = min(x, (unsigned)dpp<kHalfMirror>((int)x));
   if (TPR >= 16) x = min(x, (unsigned)dpp<kRowMirror>((int)x));
+  if (TPR >= 64)
+    x = cross_rows(x, [](unsigned a, unsigned b) { return min(a, b); });
   return x;
 }
 template <int TPR>
@@ -146,6 +169,8 @@ __device__ __forceinline__ unsigned grp_maxu(unsigned x) {
   x = max(x, (unsigned)dpp<kQuadSwap2>((int)x));
   if (TPR >= 8) x = max(x, (unsigned)dpp<kHalfMirror>((int)x));
   if (TPR >= 16) x = max(x, (unsigned)dpp<kRowMirror>((int)x));
+  if (TPR >= 64)
+    x = cross_rows(x, [](unsigned a, unsigned b) { return max(a, b); });
   return x;
 }
 
@@ -173,7 +198,9 @@ inline size_t sel_lds_bytes(int nh_max, int tpr, int W, int d) {
 // LDS, entries [j0, j0 + cnt) of the row's history at my[0 .. cnt). Sets the
 // retained history bits in wrow (LDS, OR). retain_row_regs keeps the lane's
 // L <= RV values in registers (RV = kRegVals, or kRegValsLong for the long
-// form), retain_row_lds streams them from LDS.
+// form), retain_row_lds streams them from LDS. retain_regs is the register
+// form itself: it leaves e_j in v, the lane's retained bits in mw and the
+// row's largest g in mx, for a caller that goes on with them.
 // Both find the same cut except where a tail sum F lies within its fp32
 // rounding of the threshold (they associate the sums differently).
 //
@@ -262,19 +289,19 @@ __device__ __forceinline__ void tie_share(int mine, float fhi, float thr,
   }
 }
 
-template <int TPR, int RV>
-__device__ __forceinline__ void retain_row_regs(float* my, int L, int nh,
-                                                int j0, float tau, int lane,
-                                                int part, uint32_t* wrow) {
+template <int TPR, int RV, int NW>
+__device__ __forceinline__ void retain_regs(float* my, int L, int nh,
+                                            float tau, int lane, int part,
+                                            float (&v)[RV],
+                                            unsigned (&mw)[NW], float& mx) {
   constexpr int NCK = RV / 4;
-  constexpr int NW = (RV + 31) / 32;   // mask words
+  static_assert(NW == (RV + 31) / 32, "mask words");
   const int nck = L >> 2;                         // uniform per work-group
   // Entries past the history hold -inf (the affinity pass writes the row
   // up to TPR * L), so their e is +0; the cut t* found below is never 0 (F
   // at any key up to the smallest positive e is the whole sum Z >= tau Z),
   // so zeros are never retained or counted as ties, and no validity mask
   // is needed.
-  float v[RV];
 #pragma unroll
   for (int c = 0; c < NCK; ++c) {
     f32x4 t = {};
@@ -283,7 +310,7 @@ __device__ __forceinline__ void retain_row_regs(float* my, int L, int nh,
     for (int e = 0; e < 4; ++e) v[4 * c + e] = t[e];
   }
   // (chunks c >= nck hold no entries: skipped, and +0 from here on)
-  float mx = neg_inf();
+  mx = neg_inf();
 #pragma unroll
   for (int c = 0; c < NCK; ++c)
     if (c < nck)
@@ -395,7 +422,6 @@ __device__ __forceinline__ void retain_row_regs(float* my, int L, int nh,
       }
     }
   }
-  unsigned mw[NW];
 #pragma unroll
   for (int k = 0; k < NW; ++k) mw[k] = 0u;
   if (clo - chi <= 1) {
@@ -425,6 +451,16 @@ __device__ __forceinline__ void retain_row_regs(float* my, int L, int nh,
       mw[i >> 5] |= sel ? 1u << (i & 31) : 0u;
     }
   }
+}
+
+template <int TPR, int RV>
+__device__ __forceinline__ void retain_row_regs(float* my, int L, int nh,
+                                                int j0, float tau, int lane,
+                                                int part, uint32_t* wrow) {
+  constexpr int NW = (RV + 31) / 32;
+  float v[RV], mx;
+  unsigned mw[NW];
+  retain_regs<TPR, RV, NW>(my, L, nh, tau, lane, part, v, mw, mx);
   or_bits_w<NW>(wrow, j0, mw);
 }
 
@@ -731,15 +767,29 @@ __global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(
 // prefix of i's own block) keep their exact logits, and the row is
 // normalised. A retained block therefore carries the mass
 // len_j 2^(g_ij - M) / Z with Z = sum_{m in E_i} 2^(s_im - M) +
-// sum_{j in S_i} len_j 2^(g_ij - M) (log2 units). coarse_kernel takes one
-// query-token block, one head and one pass of 16 rows; the 16 lanes of a
-// row walk its history share. The per-block masses of the pass's rows are
-// summed in row order into cpart; coarse_reduce_kernel adds a video's
-// blocks and passes in order and spreads each block's mass evenly over its
-// frames (frames never cross blocks).
-constexpr int kCoarseTPR = 16;
-constexpr int kCoarseRows = kSelThreads / kCoarseTPR;   // rows per pass
+// sum_{j in S_i} len_j 2^(g_ij - M) (log2 units). Only the query rows'
+// retention enters it, so coarse_kernel decides it itself, for those rows
+// alone, with the search of select_kernel: the affinities are computed once
+// and the retained values are still in registers when the masses are formed.
+// coarse_kernel takes one query-token block, one head and one pass of 16
+// rows, one wavefront per row (any history the mask accepts then fits a
+// lane's kRegVals registers). The grid is small (a few hundred work-groups
+// whatever the history), so latency bounds it: 16 waves share a work-group's
+// affinity tiles and every row is searched at once. The whole call (means,
+// this kernel, the reduction) takes 33 us on 256 frames x 64 tokens + 128
+// query tokens and 48 us on 1,024 frames (28/4 heads, d = 128, bf16),
+// against 183 us and 3.6 ms when the retention of every row was decided
+// first. The per-block masses of the pass's rows are summed in row order
+// into cpart; coarse_reduce_kernel adds a video's blocks and passes in order
+// and spreads each block's mass evenly over its frames (frames never cross
+// blocks).
+constexpr int kCoarseTPR = 64;
+constexpr int kCoarseThreads = 1024;
+constexpr int kCoarseWaves = kCoarseThreads / 64;
+constexpr int kCoarseRows = kCoarseThreads / kCoarseTPR;   // rows per pass
 constexpr int kCoarsePasses = kTile64 / kCoarseRows;
+static_assert(kMaxItemCandidates <= kCoarseTPR * kRegVals,
+              "a row's share of the longest history fits its registers");
 
 __device__ __forceinline__ float pair_max_(float x) {
   auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x),
@@ -753,7 +803,7 @@ __device__ __forceinline__ float pair_sum_(float x) {
 }
 
 // Log2 max and sum of row r0 + l32's exact logits over the E_i tiles e =
-// ph, ph + 4, ... (system-prefix blocks, then the row's own block).
+// ph, ph + kCoarseWaves, ... (system-prefix blocks, then the row's own block).
 template <bool F32, int D>
 __device__ __forceinline__ void exact_part(
     const DevPlan& pl, const SelCall& sc, const BlockDesc& qb, int qbid,
@@ -765,7 +815,7 @@ __device__ __forceinline__ void exact_part(
   const size_t qoff = ((size_t)(rv ? qtok : qb.start) * pl.hq + h) * D;
   mw = -__builtin_inff();
   lw = 0.f;
-  for (int e = ph; e <= nsys; e += 4) {
+  for (int e = ph; e <= nsys; e += kCoarseWaves) {
     const int kbid = e < nsys ? sys0 + e : qbid;
     const BlockDesc kb = pl.blocks[kbid];
     f32x16 s[2] = {f32x16{}, f32x16{}};
@@ -816,10 +866,11 @@ __device__ __forceinline__ void exact_part(
 }
 
 template <bool F32, int D>
-__global__ __launch_bounds__(kSelThreads) void coarse_kernel(
+__global__ __launch_bounds__(kCoarseThreads) void coarse_kernel(
     const DevPlan pl, const Workspace ws, const SelCall sc,
     float* __restrict__ cpart) {
   constexpr int TPR = kCoarseTPR, RPW = kCoarseRows;
+  constexpr int NW = (kRegVals + 31) / 32;
   extern __shared__ __attribute__((aligned(16))) float dyn[];
   const int tile = blockIdx.x, h = blockIdx.y, pass = blockIdx.z;
   const TextTile tt = pl.tiles[tile];
@@ -833,33 +884,40 @@ __global__ __launch_bounds__(kSelThreads) void coarse_kernel(
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   if (r0 >= qb.len || nh <= 0) {
-    for (int j = tid; j < Wb; j += kSelThreads) dst[j] = 0.f;
+    for (int j = tid; j < Wb; j += kCoarseThreads) dst[j] = 0.f;
     return;
   }
   const int L = sel_per_thread(nh, TPR), stride = sel_stride(nh, TPR);
   float* const ev = dyn;                      // [RPW][stride]
-  float* const emx = dyn + RPW * stride;      // [4 waves][32 rows]
-  float* const esm = emx + 4 * 32;
+  float* const emx = dyn + RPW * stride;      // [waves][32 rows]
+  float* const esm = emx + kCoarseWaves * 32;
   const int kvh = h / (pl.hq / pl.hkv);
   const int first = qbid - nh;                // first visual block
   const SeqDesc sq = pl.seqs[tt.seq];
   const int nsys = (sq.vis0 - sq.tok0 + kTile64 - 1) / kTile64;
   affinity_tiles<F32, D>(pl, ws.kbar, sc.q, sc.scale_log2, qb, h, kvh, first,
-                         nh, nh, r0, RPW, 0, wave, 4, ev, stride, lane);
+                         nh, TPR * L, r0, RPW, 0, wave, kCoarseWaves, ev,
+                         stride, lane);
+  // the E_i tiles from the last wave down (the first ones have one affinity
+  // tile more)
   float mw, lw;
-  exact_part<F32, D>(pl, sc, qb, qbid, h, kvh, first - nsys, nsys, r0, wave,
-                     lane, mw, lw);
+  exact_part<F32, D>(pl, sc, qb, qbid, h, kvh, first - nsys, nsys, r0,
+                     kCoarseWaves - 1 - wave, lane, mw, lw);
   if ((lane >> 5) == 0) {
     emx[wave * 32 + lane] = mw;
     esm[wave * 32 + lane] = lw;
   }
   __syncthreads();
-  const int rr = tid / TPR, part = tid % TPR;
-  const int row = r0 + rr;
-  if (row < qb.len) {                         // uniform over the group
-    float mE = -__builtin_inff(), lE = 0.f;   // waves' parts, in order
-    for (int w = 0; w < 4; ++w) {
-      const float m = emx[w * 32 + rr], l = esm[w * 32 + rr];
+  const int row = r0 + wave;                  // one row per wave
+  if (row < qb.len) {
+    float* const my = ev + wave * stride + lane * L;
+    float v[kRegVals], mx;
+    unsigned kept[NW];
+    retain_regs<TPR, kRegVals, NW>(my, L, nh, sc.tau, lane, lane, v, kept, mx);
+    // E_i: the waves' parts, in tile order
+    float mE = -__builtin_inff(), lE = 0.f;
+    for (int w = kCoarseWaves - 1; w >= 0; --w) {
+      const float m = emx[w * 32 + wave], l = esm[w * 32 + wave];
       if (m == -__builtin_inff()) continue;
       const float mn = fmaxf(mE, m);
       lE = (mE == -__builtin_inff() ? 0.f
@@ -867,34 +925,30 @@ __global__ __launch_bounds__(kSelThreads) void coarse_kernel(
            l * __builtin_amdgcn_exp2f(m - mn);
       mE = mn;
     }
-    const uint32_t* rbw =
-        ws.rbits + ((size_t)h * pl.nb + qbid) * pl.W * 64 + row;
-    const int j0 = part * L;
-    const int cnt = max(0, min(L, nh - j0));
-    float* const my = ev + rr * stride + j0;
-    float mx = -__builtin_inff();
-    for (int i = 0; i < cnt; ++i) {
-      const int j = j0 + i;
-      const bool kept = (rbw[(size_t)(j >> 5) * 64] >> (j & 31)) & 1u;
-      const float a = kept ? my[i] + __builtin_amdgcn_logf(
-                                         (float)pl.blocks[first + j].len)
-                           : -__builtin_inff();
-      my[i] = a;
-      mx = fmaxf(mx, a);
-    }
-    const float M = fmaxf(grp_max<TPR>(mx), mE);
+    // a history block holds 64 tokens, except the video's last visual one
+    const int jl = (sq.txt0 - sq.vis0 + kTile64 - 1) / kTile64 - 1 - lane * L;
+    const float last = (float)pl.blocks[first + jl + lane * L].len;
+    const float M = fmaxf(mx + 6.f, mE);      // 6 = log2(64)
+    const float up = __builtin_amdgcn_exp2f(mx - M);
     float z = 0.f;
-    for (int i = 0; i < cnt; ++i) {
-      const float w = __builtin_amdgcn_exp2f(my[i] - M);
-      my[i] = w;
-      z += w;
+#pragma unroll
+    for (int i = 0; i < kRegVals; ++i) {
+      const float len = i == jl ? last : (float)kTile64;
+      v[i] = (kept[i >> 5] >> (i & 31)) & 1u ? v[i] * up * len : 0.f;
+      z += v[i];
     }
     z = grp_sum<TPR>(z) + lE * __builtin_amdgcn_exp2f(mE - M);
     const float inv = 1.f / z;
-    for (int i = 0; i < cnt; ++i) my[i] *= inv;
+#pragma unroll
+    for (int c = 0; c < kRegVals / 4; ++c)
+      if (4 * c < L) {
+        const f32x4 t = {v[4 * c] * inv, v[4 * c + 1] * inv,
+                         v[4 * c + 2] * inv, v[4 * c + 3] * inv};
+        *(f32x4*)(my + 4 * c) = t;
+      }
   }
   __syncthreads();
-  for (int j = tid; j < Wb; j += kSelThreads) {
+  for (int j = tid; j < Wb; j += kCoarseThreads) {
     float t = 0.f;
     if (j < nh)
       for (int r = 0; r < RPW && r0 + r < qb.len; ++r) t += ev[r * stride + j];
@@ -979,8 +1033,10 @@ size_t select_lds_need(int nh_max, int W) {
   return sel_lds_bytes(nh_max, 16, W, 128);
 }
 
-hipError_t launch_select(const DevPlan& p, const Workspace& w,
-                         const SelCall& c, hipStream_t s) {
+namespace {
+
+hipError_t launch_pool(const DevPlan& p, const Workspace& w, const SelCall& c,
+                       hipStream_t s) {
   if (c.fp32) {
     if (c.d == 64)
       pool_kernel<true, 64><<<dim3(p.nb, p.hkv), dim3(64), 0, s>>>(p, c.k,
@@ -996,7 +1052,14 @@ hipError_t launch_select(const DevPlan& p, const Workspace& w,
       pool_kernel<false, 128><<<dim3(p.nb, p.hkv), dim3(128), 0, s>>>(
           p, c.k, w.kbar);
   }
-  hipError_t e = hipGetLastError();
+  return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_select(const DevPlan& p, const Workspace& w,
+                         const SelCall& c, hipStream_t s) {
+  const hipError_t e = launch_pool(p, w, c, s);
   if (e != hipSuccess) return e;
   const int nh_max = std::max(p.hmax, 1);
   if (c.fp32)
@@ -1013,22 +1076,24 @@ size_t coarse_part_floats(int n_tiles, int hq, int W) {
 hipError_t launch_coarse(const DevPlan& p, const Workspace& w,
                          const SelCall& c, float* cpart, float* out,
                          hipStream_t s) {
+  hipError_t e = launch_pool(p, w, c, s);
+  if (e != hipSuccess) return e;
   if (p.n_tiles > 0) {
     const int nh_max = std::max(p.hmax, 1);
-    const size_t lds = (size_t)kCoarseRows *
-                           sel_stride(nh_max, kCoarseTPR) * 4 + 2 * 4 * 32 * 4;
-    dim3 grid(p.n_tiles, p.hq, kCoarsePasses), block(kSelThreads);
+    const size_t lds =
+        (size_t)kCoarseRows * sel_stride(nh_max, kCoarseTPR) * 4 +
+        2 * kCoarseWaves * 32 * 4;
+    dim3 grid(p.n_tiles, p.hq, kCoarsePasses), block(kCoarseThreads);
     auto go = [&](auto fn) -> hipError_t {
       if (lds > 64 * 1024) {
-        hipError_t e = hipFuncSetAttribute(
+        const hipError_t e2 = hipFuncSetAttribute(
             (const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize,
             (int)lds);
-        if (e != hipSuccess) return e;
+        if (e2 != hipSuccess) return e2;
       }
       fn<<<grid, block, lds, s>>>(p, w, c, cpart);
       return hipGetLastError();
     };
-    hipError_t e;
     if (c.fp32)
       e = c.d == 64 ? go(coarse_kernel<true, 64>) : go(coarse_kernel<true, 128>);
     else

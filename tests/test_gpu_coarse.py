@@ -54,6 +54,26 @@ CASES = {
 }
 
 
+# The query rows' histories at the edges of a lane's share (64 lanes per row,
+# shares in steps of four blocks): one block, a full step and one past it, a
+# short last visual block, and the longest history a mask accepts (2,047
+# blocks, with one to spare for the row's own).
+EDGES = {
+    "one_block": _w("one-block", n_frames=(1,), n_text=(3,), n_sys=(0,),
+                    plant_args={"count": 1, "s_frame": (2.0, 3.0),
+                                "s_query": 2.0}),
+    "share_4": _w("share-4", hq=2, tokens_per_frame=64, n_frames=(256,),
+                  n_text=(17,), n_sys=(0,)),
+    "share_8_short": _w("share-8-short", hq=2, tokens_per_frame=16,
+                        n_frames=(1027,), n_text=(80,), n_sys=(65,)),
+    "fp32_share_8": _w("fp32-share-8", dtype="fp32", hq=2, hkv=1,
+                       tokens_per_frame=64, n_frames=(300,), n_text=(5,),
+                       n_sys=(130,)),
+    "longest": _w("longest", d=64, hq=2, tokens_per_frame=64,
+                  n_frames=(2046,), n_text=(70,), n_sys=(0,)),
+}
+
+
 def _layout(w):
     ns, nf, nt = wl.layout_arrays(w)
     return Layout(ns, nf, nt, w.tokens_per_frame)
@@ -72,9 +92,17 @@ def _gpu_coarse(w, mask, l=0):
     return out.cpu().numpy().astype(np.float64)
 
 
+@pytest.mark.parametrize("name", list(EDGES))
+def test_coarse_evidence_history_edges(name):
+    _check_coarse(name, EDGES[name])
+
+
 @pytest.mark.parametrize("name", list(CASES))
 def test_coarse_evidence(name):
-    w = CASES[name]
+    _check_coarse(name, CASES[name])
+
+
+def _check_coarse(name, w):
     ev = pytest.ev
     say(f"case {name}")
     lay = _layout(w)
