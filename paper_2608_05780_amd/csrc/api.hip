@@ -177,6 +177,9 @@ evisel_status upload(evisel_mask* m, hipStream_t s) {
   for (int32_t loc : P.blk_local) hmax = std::max(hmax, loc);
   dp.hmax = hmax;
   dp.topp = P.rule.tau > 0.f ? 1 : 0;
+  dp.max_frames = 0;
+  for (const auto& sq : P.seqs)
+    dp.max_frames = std::max(dp.max_frames, sq.n_frames);
   return EVISEL_OK;
 }
 
@@ -700,15 +703,10 @@ evisel_status evisel_frame_evidence(const evisel_mask* m,
                     "top-k supports at most 65536 frames per video");
   if (e_ff && !frame_pairs)
     return fail(EVISEL_ERR_INVALID_ARG, "e_ff needs frame_pairs");
-  hipError_t e = evisel::launch_frame_evidence(m->dp, evidence, n_layers,
-                                               e_qf_layer, e_qf, k_per_seq,
-                                               topk_idx, (hipStream_t)stream);
+  const hipError_t e = evisel::launch_frame_evidence(
+      m->dp, evidence, n_layers, e_qf_layer, e_qf, k_per_seq, topk_idx,
+      frame_pairs, e_ff, (hipStream_t)stream);
   if (e != hipSuccess) return hip_fail(e, "frame evidence launch");
-  if (e_ff) {
-    e = evisel::launch_e_ff(m->dp, frame_pairs, n_layers, e_ff,
-                            (hipStream_t)stream);
-    if (e != hipSuccess) return hip_fail(e, "e_ff launch");
-  }
   return EVISEL_OK;
 }
 

@@ -21,9 +21,13 @@
 //   partials the same way: the largest chunk reference, then the rescaled
 //   chunk row sums added in chunk order. The evidence part computes the
 //   LSE of the rows its frames read once into LDS (when they fit).
-// frame_mean_kernel: E_qf[l, t] = sum_h E[l, h, t] / (Hq * n_text) and the
-//   mean over layers (heads averaged per layer, layer kept); 32 frames x 32
-//   layer groups per work-group, layers added in a fixed order.
+// frame_mean_kernel: one launch, two independent parts (ranges of the block
+//   index):
+//   means      E_qf[l, t] = sum_h E[l, h, t] / (Hq * n_text) and the mean
+//              over layers (heads averaged per layer, layer kept); 32 frames
+//              x 32 layer groups per work-group, layers added in a fixed
+//              order;
+//   E_ff       when requested, see e_ff_part.
 // topk_kernel: per video, rank r(t) = #{t' : e(t') > e(t) or (e(t') == e(t)
 //   and t' < t)}; frames with r(t) < k land at topk[offset + r(t)]. Ranks of a
 //   strict total order are a permutation, so every slot gets one writer.
@@ -229,11 +233,89 @@ __global__ __launch_bounds__(kCeThreads) void combine_evidence_kernel(
 }
 
 constexpr int kFmFrames = 32, kFmLayers = 32;
+constexpr int kFmThreads = kFmFrames * kFmLayers;
 
-__global__ __launch_bounds__(kFmFrames * kFmLayers) void frame_mean_kernel(
+// E_ff[l, t]: the mean over t's earlier frames of A_ff[t, b] and the mean
+// over its later frames of A_ff[a, t], averaged over the sides that exist
+// (pairs outside the sparse pattern are 0). One wavefront per frame and
+// kEffLayers layers: the frame's pair indexes are read once and the layers'
+// values are in flight together, so the chain of dependent reads (offsets,
+// indexes, values) is paid once per kEffLayers layers. Lanes take strided
+// pairs, then a butterfly adds the lanes (fixed order, every lane ends with
+// the same bits).
+constexpr int kEffLayers = 7, kEffRuns = 4;
+
+__device__ __forceinline__ void e_ff_part(const DevPlan& pl,
+                                          const float* __restrict__ pr,
+                                          int n_layers, int wv,
+                                          float* __restrict__ e_ff) {
+  const int lane = threadIdx.x & 63;
+  const int n_lg = (n_layers + kEffLayers - 1) / kEffLayers;
+  const int t = wv / n_lg, l0 = (wv % n_lg) * kEffLayers;
+  if (t >= pl.T) return;
+  const int o0 = pl.ff_out_ptr[t], o1 = pl.ff_out_ptr[t + 1];
+  const int i0 = pl.ff_in_ptr[t], i1 = pl.ff_in_ptr[t + 1];
+  const SeqDesc sq = pl.seqs[pl.frame_seq[t]];
+  float o[kEffLayers], in[kEffLayers];
+#pragma unroll
+  for (int u = 0; u < kEffLayers; ++u) o[u] = in[u] = 0.f;
+  // four runs of 64 pairs at a time: a sink frame is the key frame of every
+  // later frame, and its list would be a chain of as many round trips
+  auto side = [&](const int* idx, int a, int b, float (&acc)[kEffLayers]) {
+    for (int i = a + lane; i < b; i += 64 * kEffRuns) {
+      int ix[kEffRuns];
+      float x[kEffRuns][kEffLayers];
+#pragma unroll
+      for (int r = 0; r < kEffRuns; ++r)
+        ix[r] = i + 64 * r < b ? idx[i + 64 * r] : -1;
+#pragma unroll
+      for (int r = 0; r < kEffRuns; ++r)
+#pragma unroll
+        for (int u = 0; u < kEffLayers; ++u)
+          x[r][u] = ix[r] >= 0 && l0 + u < n_layers
+                        ? pr[(size_t)(l0 + u) * pl.n_pairs + ix[r]]
+                        : 0.f;
+#pragma unroll
+      for (int r = 0; r < kEffRuns; ++r)
+#pragma unroll
+        for (int u = 0; u < kEffLayers; ++u) acc[u] += x[r][u];
+    }
+  };
+  side(pl.ff_out_idx, o0, o1, o);
+  side(pl.ff_in_idx, i0, i1, in);
+  const int tl = t - sq.frame0, F = sq.n_frames;
+#pragma unroll
+  for (int u = 0; u < kEffLayers; ++u) {
+    if (l0 + u >= n_layers) break;
+    const float so = wave_sum(o[u]), si = wave_sum(in[u]);
+    float acc = 0.f;
+    int ns = 0;
+    if (tl > 0) {
+      acc += so / (float)tl;
+      ++ns;
+    }
+    if (tl < F - 1) {
+      acc += si / (float)(F - 1 - tl);
+      ++ns;
+    }
+    if (lane == 0)
+      e_ff[(size_t)(l0 + u) * pl.T + t] = ns ? acc / (float)ns : 0.f;
+  }
+}
+
+__global__ __launch_bounds__(kFmThreads) void frame_mean_kernel(
     const DevPlan pl, const float* __restrict__ ev, int n_layers,
-    float* __restrict__ e_layer, float* __restrict__ e_qf) {
+    float* __restrict__ e_layer, float* __restrict__ e_qf,
+    const float* __restrict__ pairs, float* __restrict__ e_ff) {
   __shared__ float red[kFmLayers][kFmFrames];
+  const int n_mean = (pl.T + kFmFrames - 1) / kFmFrames;
+  if ((int)blockIdx.x >= n_mean) {
+    e_ff_part(pl, pairs, n_layers,
+              ((int)blockIdx.x - n_mean) * (kFmThreads / 64) +
+                  (int)(threadIdx.x >> 6),
+              e_ff);
+    return;
+  }
   const int tl = threadIdx.x % kFmFrames, lg = threadIdx.x / kFmFrames;
   const int t = blockIdx.x * kFmFrames + tl;
   float part = 0.f;
@@ -242,7 +324,8 @@ __global__ __launch_bounds__(kFmFrames * kFmLayers) void frame_mean_kernel(
     const float denom = (float)pl.hq * (float)sq.n_text;
     for (int l = lg; l < n_layers; l += kFmLayers) {
       float s = 0.f;
-#pragma unroll 4
+      // fourteen heads' loads in flight at a time
+#pragma unroll 14
       for (int h = 0; h < pl.hq; ++h)
         s += ev[((size_t)l * pl.hq + h) * pl.T + t];
       const float v = s / denom;
@@ -260,40 +343,84 @@ __global__ __launch_bounds__(kFmFrames * kFmLayers) void frame_mean_kernel(
   }
 }
 
-constexpr int kTopkThreads = 1024;
-constexpr int kTopkLds = 16384;   // frames held in LDS per video
-
 __device__ __forceinline__ float rank_key(float x) {
   return x != x ? -__builtin_inff() : x;   // NaN ranks like -inf
 }
 
+// One work-group per video and 64 of its frames (lane = frame): the video's
+// scores pass through LDS kTopkChunk at a time, every wavefront counts those
+// of its share that rank before the lane's frame (ties before it in frame
+// order: >= among the frames before the work-group's own 64, > after them),
+// and the wavefronts' counts are added. A frame costs two instructions per
+// score and wavefront; one work-group per video (each frame against all
+// scores, one LDS read each) took 60 us on 1,024 frames.
+constexpr int kTopkFrames = 64;
+constexpr int kTopkThreads = 512;
+constexpr int kTopkWaves = kTopkThreads / 64;
+constexpr int kTopkChunk = 4096;
+
 __global__ __launch_bounds__(kTopkThreads) void topk_kernel(
     const DevPlan pl, const float* __restrict__ e_qf,
     const int* __restrict__ kps, int* __restrict__ topk) {
-  __shared__ float vals[kTopkLds];
+  __shared__ __attribute__((aligned(16))) float vals[kTopkChunk];
+  __shared__ int part[kTopkWaves][64];
   const int n = blockIdx.x;
   const SeqDesc sq = pl.seqs[n];
-  const int F = sq.n_frames;
-  int off = 0;
-  for (int i = 0; i < n; ++i) off += min(max(kps[i], 0), pl.seqs[i].n_frames);
+  const int F = sq.n_frames, f0 = blockIdx.y * kTopkFrames;
+  if (f0 >= F) return;
   const int k = min(max(kps[n], 0), F);
   if (k == 0) return;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const float* src = e_qf + sq.frame0;
-  const bool in_lds = F <= kTopkLds;
-  if (in_lds) {
-    for (int t = threadIdx.x; t < F; t += kTopkThreads)
-      vals[t] = rank_key(src[t]);
+  const int t = f0 + lane;
+  const float v = rank_key(src[min(t, F - 1)]);
+  int rank = 0;
+  for (int c0 = 0; c0 < F; c0 += kTopkChunk) {
+    const int m = min(kTopkChunk, F - c0);
+    if (c0) __syncthreads();
+    // past the end: NaN, which no comparison counts
+    const int m4 = (m + 3) & ~3;
+    for (int i = tid; i < m4; i += kTopkThreads)
+      vals[i] = i < m ? rank_key(src[c0 + i]) : __builtin_nanf("");
     __syncthreads();
-  }
-  for (int t = threadIdx.x; t < F; t += kTopkThreads) {
-    const float v = in_lds ? vals[t] : rank_key(src[t]);
-    int rank = 0;
-    for (int u = 0; u < F; ++u) {
-      const float w = in_lds ? vals[u] : rank_key(src[u]);
-      rank += (w > v) || (w == v && u < t);
+    // this wave's share, in fours: before the 64 frames, among them, after
+    const int per = ((m4 >> 2) + kTopkWaves - 1) / kTopkWaves;
+    const int a = min(wave * per, m4 >> 2) * 4;
+    const int b = min((wave + 1) * per, m4 >> 2) * 4;
+    const int lo = min(max(f0 - c0, a), b);           // multiples of 4
+    const int hi = min(max(f0 + kTopkFrames - c0, a), b);
+    typedef float f4 __attribute__((ext_vector_type(4)));
+    for (int i = a; i < lo; i += 4) {
+      const f4 w = *(const f4*)(vals + i);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) rank += w[e] >= v;
     }
-    if (rank < k) topk[off + rank] = t;
+    for (int i = lo; i < hi; i += 4) {
+      const f4 w = *(const f4*)(vals + i);
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        rank += w[e] > v || (w[e] == v && c0 + i + e < t);
+    }
+    for (int i = hi; i < b; i += 4) {
+      const f4 w = *(const f4*)(vals + i);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) rank += w[e] > v;
+    }
   }
+  part[wave][lane] = rank;
+  __syncthreads();
+  if (wave) return;
+  rank = 0;
+#pragma unroll
+  for (int w = 0; w < kTopkWaves; ++w) rank += part[w][lane];
+  // output offset: the earlier videos' counts
+  int off = 0;
+  for (int i = lane; i < n; i += 64)
+    off += min(max(kps[i], 0), pl.seqs[i].n_frames);
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) off += __shfl_xor(off, o);
+  if (t < F && rank < k) topk[off + rank] = t;
 }
 
 // Cross-frame cue of one layer: one wavefront per frame pair (a, b). Lane r
@@ -356,45 +483,6 @@ __global__ __launch_bounds__(64 * kPairWaves) void frame_pairs_kernel(
   if (lane == 0) out[pi] = acc / ((float)pl.hq * (float)pl.Nv);
 }
 
-// E_ff[l, t]: the mean over t's earlier frames of A_ff[t, b] and the mean
-// over its later frames of A_ff[a, t], averaged over the sides that exist
-// (pairs outside the sparse pattern are 0). One wavefront per (layer,
-// frame): lanes take strided pairs, then a butterfly adds the lanes (fixed
-// order, every lane ends with the same bits).
-constexpr int kEffWaves = 4;
-
-__global__ __launch_bounds__(64 * kEffWaves) void e_ff_kernel(
-    const DevPlan pl, const float* __restrict__ pr, float* __restrict__ e_ff) {
-  const int lane = threadIdx.x & 63;
-  const int t = blockIdx.x * kEffWaves + (threadIdx.x >> 6), l = blockIdx.y;
-  if (t >= pl.T) return;
-  const SeqDesc sq = pl.seqs[pl.frame_seq[t]];
-  const int tl = t - sq.frame0, F = sq.n_frames;
-  const float* p = pr + (size_t)l * pl.n_pairs;
-  float o = 0.f, in = 0.f;
-  for (int i = pl.ff_out_ptr[t] + lane; i < pl.ff_out_ptr[t + 1]; i += 64)
-    o += p[pl.ff_out_idx[i]];
-  for (int i = pl.ff_in_ptr[t] + lane; i < pl.ff_in_ptr[t + 1]; i += 64)
-    in += p[pl.ff_in_idx[i]];
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) {
-    o += __shfl_xor(o, m);
-    in += __shfl_xor(in, m);
-  }
-  if (lane) return;
-  float acc = 0.f;
-  int ns = 0;
-  if (tl > 0) {
-    acc += o / (float)tl;
-    ++ns;
-  }
-  if (tl < F - 1) {
-    acc += in / (float)(F - 1 - tl);
-    ++ns;
-  }
-  e_ff[(size_t)l * pl.T + t] = ns ? acc / (float)ns : 0.f;
-}
-
 }  // namespace
 
 hipError_t launch_frame_pairs(const DevPlan& p, const Workspace& w,
@@ -402,13 +490,6 @@ hipError_t launch_frame_pairs(const DevPlan& p, const Workspace& w,
   if (p.n_pairs == 0) return hipSuccess;
   frame_pairs_kernel<<<dim3((p.n_pairs + kPairWaves - 1) / kPairWaves),
                        dim3(64 * kPairWaves), 0, s>>>(p, w, pairs_out);
-  return hipGetLastError();
-}
-
-hipError_t launch_e_ff(const DevPlan& p, const float* pairs,
-                       int32_t n_layers, float* e_ff, hipStream_t s) {
-  e_ff_kernel<<<dim3((p.T + kEffWaves - 1) / kEffWaves, n_layers),
-                dim3(64 * kEffWaves), 0, s>>>(p, pairs, e_ff);
   return hipGetLastError();
 }
 
@@ -439,14 +520,23 @@ hipError_t launch_combine_evidence(const DevPlan& p, const Workspace& w,
 hipError_t launch_frame_evidence(const DevPlan& p, const float* evidence,
                                  int32_t n_layers, float* e_qf_layer,
                                  float* e_qf, const int32_t* k_per_seq,
-                                 int32_t* topk, hipStream_t s) {
-  frame_mean_kernel<<<dim3((p.T + kFmFrames - 1) / kFmFrames),
-                      dim3(kFmFrames * kFmLayers), 0, s>>>(
-      p, evidence, n_layers, e_qf_layer, e_qf);
+                                 int32_t* topk, const float* pairs,
+                                 float* e_ff, hipStream_t s) {
+  int64_t blocks = (p.T + kFmFrames - 1) / kFmFrames;
+  if (e_ff) {
+    constexpr int kWaves = kFmThreads / 64;
+    const int64_t waves =
+        (int64_t)p.T * ((n_layers + kEffLayers - 1) / kEffLayers);
+    blocks += (waves + kWaves - 1) / kWaves;
+  }
+  if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
+  frame_mean_kernel<<<dim3((unsigned)blocks), dim3(kFmThreads), 0, s>>>(
+      p, evidence, n_layers, e_qf_layer, e_qf, pairs, e_ff);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || !k_per_seq) return e;
-  topk_kernel<<<dim3(p.n_seq), dim3(kTopkThreads), 0, s>>>(p, e_qf, k_per_seq,
-                                                           topk);
+  // (at most 65,536 frames per video: 1,024 in y)
+  topk_kernel<<<dim3(p.n_seq, (p.max_frames + kTopkFrames - 1) / kTopkFrames),
+                dim3(kTopkThreads), 0, s>>>(p, e_qf, k_per_seq, topk);
   return hipGetLastError();
 }
 

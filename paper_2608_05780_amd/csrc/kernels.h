@@ -33,6 +33,7 @@ struct DevPlan {
   int32_t W;                 // history words per row (top-p)
   int32_t hmax;              // longest block history (top-p)
   int32_t topp;              // 1: adaptive top-p retention
+  int32_t max_frames;        // frames of the longest video
 };
 
 // Workspace carve-up for one prefill call.
@@ -109,18 +110,19 @@ hipError_t launch_seg_fill(const DevPlan& p, const Workspace& w,
 hipError_t launch_combine_evidence(const DevPlan& p, const Workspace& w,
                                    const AttnCall& c, float* evidence_layer,
                                    float* text_mass_layer, hipStream_t s);
+// Head and layer means, the top-k frames (k_per_seq not null) and E_ff
+// [n_layers][T] from the cross-frame pairs [n_layers][n_pairs] (e_ff not
+// null).
 hipError_t launch_frame_evidence(const DevPlan& p, const float* evidence,
                                  int32_t n_layers, float* e_qf_layer,
                                  float* e_qf, const int32_t* k_per_seq,
-                                 int32_t* topk, hipStream_t s);
+                                 int32_t* topk, const float* pairs,
+                                 float* e_ff, hipStream_t s);
 // Cross-frame cue of one layer: pairs_out[i] = A_ff of pair i.
 hipError_t launch_frame_pairs(const DevPlan& p, const Workspace& w,
                               float* pairs_out, hipStream_t s);
 // Intra-frame cue of one layer: out [T][N_v][N_v].
 hipError_t launch_intra_frame(const DevPlan& p, const Workspace& w,
                               const AttnCall& c, float* out, hipStream_t s);
-// E_ff [n_layers][T] from the cross-frame pairs [n_layers][n_pairs].
-hipError_t launch_e_ff(const DevPlan& p, const float* pairs,
-                       int32_t n_layers, float* e_ff, hipStream_t s);
 
 }  // namespace evisel
