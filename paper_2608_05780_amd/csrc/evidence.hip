@@ -243,7 +243,7 @@ constexpr int kFmThreads = kFmFrames * kFmLayers;
 // indexes, values) is paid once per kEffLayers layers. Lanes take strided
 // pairs, then a butterfly adds the lanes (fixed order, every lane ends with
 // the same bits).
-constexpr int kEffLayers = 7, kEffRuns = 4;
+constexpr int kEffLayers = 4, kEffRuns = 8;
 
 __device__ __forceinline__ void e_ff_part(const DevPlan& pl,
                                           const float* __restrict__ pr,
