@@ -22,7 +22,7 @@
 // free of LDS bank conflicts.
 //
 // Per key tile (64 keys):
-//   S^T = K Q^T        32x32x16 bf16 MFMA (fp32 inputs: 32x32x2 f32 MFMA);
+//   S^T = K Q^T        32x32x16 bf16 MFMA (fp32 inputs: attn_f32.h);
 //                      computing the transpose leaves one query row per lane
 //                      (lane % 32); a row max or sum is an in-lane reduction
 //                      plus one v_permlane32_swap with lane ^ 32.
@@ -69,6 +69,7 @@
 #include <algorithm>
 #include <type_traits>
 
+#include "attn_f32.h"
 #include "attn_tiles.h"
 #include "kernels.h"
 
@@ -81,13 +82,19 @@ __global__ __attribute__((amdgpu_flat_work_group_size(kThreads, kThreads),
                           amdgpu_waves_per_eu(2, 2))) void
 attn_kernel(const DevPlan pl, const Workspace ws, const AttnCall ac) {
   using T = typename P::T;
+  constexpr bool F32 = sizeof(T) == 4;
   constexpr int TB = kTile * P::RC * 16;   // bytes of one tile
-  constexpr int VSWZ = sizeof(T) == 2 ? kSwzV : kSwzNone;
-  __shared__ __attribute__((aligned(1024))) char smem[4 * TB];
+  constexpr int VSWZ = kSwzV;
+  __shared__ __attribute__((
+      aligned(1024))) char smem[F32 ? F32Split<D>::kSmem : 4 * TB];
   EV_LDS char* lds = (EV_LDS char*)smem;   // [K0 | K1 | V0 | V1]
   // top-p: CSR positions of the item's key tiles that some row retained
   __shared__ short clist[TOPP ? kMaxItemCandidates : 1];
   __shared__ int n_kept;
+  if constexpr (F32) {
+    attn_f32_item<D, TOPP>(pl, ws, ac, smem, clist, &n_kept);
+    return;
+  } else {
 
   const WorkItem it = pl.items[blockIdx.x];
   if (it.qblock < 0) return;
@@ -117,7 +124,6 @@ attn_kernel(const DevPlan pl, const Workspace ws, const AttnCall ac) {
   const T* vg = (const T*)ac.v;
 
   typename P::QFrag qf;
-  if constexpr (!P::kStaged) P::load_q(qf, ac.q, qpos, qvalid, h, pl.hq, g);
 
   float m_ref = neg_inf(), l_part = 0.f, nv_part = 0.f;
   f32x16 o[D / 32];
@@ -197,7 +203,7 @@ attn_kernel(const DevPlan pl, const Workspace ws, const AttnCall ac) {
   // the first tile's start one round trip after the kernel does. Without
   // top-p the first descriptor batch is fetched in the same round trip.
   if constexpr (!TOPP) load_batch(0);
-  if constexpr (P::kStaged) {
+  {
     TileLoader<T, D, kSwzK> qload;
     qload.init(pl.hq, wave, lane);
     qload.issue(kbuf(1), (const T*)ac.q, it.q0start, it.q0len, it.head, wave);
@@ -405,11 +411,9 @@ attn_kernel(const DevPlan pl, const Workspace ws, const AttnCall ac) {
   int lnext = loc_of(0), pnext = pos_of(0);
   unsigned wnext = 0u;
   if (TOPP && n > 0) wnext = row_bits(lnext);
-  if constexpr (P::kStaged) {
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();   // Q rows visible to every wave
-    P::load_q_lds(qf, hsub ? vbuf(1) : kbuf(1), qrow, g);
-  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();   // Q rows visible to every wave
+  P::load_q_lds(qf, hsub ? vbuf(1) : kbuf(1), qrow, g);
   // Tile j lives in buffer pair j % 2. The loop is unrolled by two so that
   // each copy addresses fixed buffers: their LDS offsets become instruction
   // immediates instead of a VALU add per operand read.
@@ -473,7 +477,7 @@ attn_kernel(const DevPlan pl, const Workspace ws, const AttnCall ac) {
     if (j + 1 < n) step(j + 1, std::integral_constant<int, 1>{});
   }
   const float l_tot = pair_sum(l_part);
-  if (P::kStaged && !is_text) {
+  if (!is_text) {
     // O rows through LDS (K0 for the first head, K1 for the second), then
     // whole-row stores by every thread of the work-group
     __syncthreads();   // every wave is done with the last tile
@@ -487,17 +491,6 @@ attn_kernel(const DevPlan pl, const Workspace ws, const AttnCall ac) {
 
   if (!is_text) {
     if (qvalid) {
-      if constexpr (!P::kStaged) {
-        const float inv = 1.f / l_tot;
-#pragma unroll
-        for (int mt = 0; mt < D / 32; ++mt)
-#pragma unroll
-          for (int r4 = 0; r4 < 4; ++r4) {
-            f32x4 v = {o[mt][4 * r4] * inv, o[mt][4 * r4 + 1] * inv,
-                       o[mt][4 * r4 + 2] * inv, o[mt][4 * r4 + 3] * inv};
-            P::store_o(ac.o, qpos, h, pl.hq, 32 * mt + 8 * r4 + 4 * g, v);
-          }
-      }
       if (g == 0 && ac.lse)
         ac.lse[(size_t)h * pl.S + qpos] = (m_ref + log2_(l_tot)) * kLn2;
       if (g == 0 && ac.lse2v)
@@ -525,6 +518,7 @@ attn_kernel(const DevPlan pl, const Workspace ws, const AttnCall ac) {
       }
     }
   }
+  }   // bf16
 }
 
 // ---------------------------------------------------------------------------

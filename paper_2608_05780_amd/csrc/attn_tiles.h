@@ -253,16 +253,10 @@ struct Bf16Path {
     __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
   }
 
-  __device__ static void store_o(void* out, int qpos, int h, int hq, int d0,
-                                 f32x4 v) {
-    bf16x4 b = __builtin_convertvector(v, bf16x4);
-    *(bf16x4*)((__bf16*)out + ((size_t)qpos * hq + h) * D + d0) = b;
-  }
   // Q and O move through LDS in the K-tile layout (rows of RC swizzled
   // 16-byte chunks), so that every global access is a whole row: 16 lanes
   // cover one row of one head. Q arrives by the same direct global -> LDS
   // loads as the key tiles.
-  static constexpr bool kStaged = true;
   static constexpr int kPer = kTile * RC / kThreads;   // chunks per thread
 
   // The B operand of row `row` from a staged Q tile (as load_q).
@@ -311,9 +305,9 @@ struct Bf16Path {
 };
 
 // ---------------------------------------------------------------------------
-// fp32 operands (32x32x2 f32 MFMA). The contraction over d pairs element t
-// of lane half g with d = g*D/2 + t, so every lane reads contiguous runs.
-// V needs no transpose: each lane contributes one value per k-step.
+// fp32 operands of the intra-frame cue (32x32x2 f32 MFMA). The contraction
+// over d pairs element t of lane half g with d = g*D/2 + t, so every lane
+// reads contiguous runs.
 template <int D>
 struct F32Path {
   using T = float;
@@ -350,39 +344,6 @@ struct F32Path {
       }
     }
   }
-
-  struct PvOff {
-    int lane;
-  };
-  __device__ static void pv_offsets(PvOff& po, int lane) { po.lane = lane; }
-  __device__ static void pv(f32x16 (&o)[D / 32], const EV_LDS char* vt,
-                            const f32x16 (&p)[2], const PvOff& po) {
-    const int lane = po.lane;
-    const int l32 = lane & 31, g = lane >> 5;
-#pragma unroll
-    for (int c = 0; c < 2; ++c) {
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int key = 32 * c + 8 * (r >> 2) + 4 * g + (r & 3);
-#pragma unroll
-        for (int mt = 0; mt < D / 32; ++mt)
-          o[mt] = __builtin_amdgcn_mfma_f32_32x32x2f32(
-              *(const EV_LDS float*)(vt + key * RC * 16 + (32 * mt + l32) * 4),
-              p[c][r], o[mt], 0, 0, 0);
-      }
-    }
-  }
-
-  __device__ static void store_o(void* out, int qpos, int h, int hq, int d0,
-                                 f32x4 v) {
-    *(f32x4*)((float*)out + ((size_t)qpos * hq + h) * D + d0) = v;
-  }
-  static constexpr bool kStaged = false;
-  __device__ static void load_q_lds(QFrag&, const EV_LDS char*, int, int) {}
-  __device__ static void o_to_lds(EV_LDS char*, const f32x16 (&)[D / 32],
-                                  float, int, int) {}
-  __device__ static void o_from_lds(void*, const EV_LDS char*, int, int, int,
-                                    int, int) {}
 };
 
 
