@@ -337,6 +337,30 @@ std::string build_plan(const Layout& L, const Rule& R, int32_t hq, int32_t hkv,
     for (const Item& it : groups[gc.second]) q[x].push_back(it.w);
     load[x] += gc.first;
   }
+  if (window < 0) {
+    // Every causal block is a key tile, so the items' lengths run from one
+    // tile to the whole video and contiguous runs of equal cost would leave
+    // one queue with few items, all long (256 frames, top-p: 304 items of 180
+    // to 257 tiles on 64 slots, the queue done 14 % late). The items are dealt
+    // longest first to the emptiest queue among those of their kv head (whose
+    // keys and values each L2 then fetches once); where the kv heads do not
+    // divide the queues, among all. Neighbouring rows share nearly all their
+    // tiles wherever they run.
+    std::stable_sort(other_items.begin(), other_items.end(),
+                     [](const Item& a, const Item& b) {
+                       return a.cost > b.cost;
+                     });
+    const int per = hkv <= kXcds && kXcds % hkv == 0 ? kXcds / hkv : kXcds;
+    for (const Item& it : other_items) {
+      const int x0 = per == kXcds ? 0 : it.w.head / group * per;
+      const int x = (int)(std::min_element(load.begin() + x0,
+                                           load.begin() + x0 + per) -
+                          load.begin());
+      q[x].push_back(it.w);
+      load[x] += it.cost;
+    }
+    other_items.clear();
+  }
   int64_t rest = 0;
   for (const Item& it : other_items) rest += it.cost;
   const int64_t all = rest + std::accumulate(load.begin(), load.end(),
