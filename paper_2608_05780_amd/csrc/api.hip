@@ -44,6 +44,46 @@ evisel_status hip_fail(hipError_t e, const char* what) {
 
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
+struct WsLayout {
+  size_t pO, pM, pL, pNV, seg, kbar, rbits, ubits, cpart, total;
+  size_t segv, lse2v, intra_part, cue_total;   // frame cues, after `total`
+};
+
+WsLayout ws_layout(const evisel::Plan& P, int32_t d) {
+  WsLayout w{};
+  size_t off = 0;
+  auto take = [&](size_t bytes) {
+    const size_t o = off;
+    off += align256(bytes);
+    return o;
+  };
+  const size_t rows = (size_t)P.n_slots * 64;
+  w.pO = take(rows * d * 4);
+  w.pM = take(rows * 4);
+  w.pL = take(rows * 4);
+  w.pNV = take(rows * 4);
+  w.seg = take((size_t)P.hq * P.segtot * 4);
+  if (P.rule.tau > 0.f) {
+    const size_t nb = P.blocks.size();
+    // bf16 keeps hi and lo (2 x 2 bytes), fp32 one float: 4 bytes either way
+    w.kbar = take((size_t)P.hkv * nb * d * 4);
+    w.rbits = take((size_t)P.hq * nb * P.hist_words * 64 * 4);
+    w.ubits = take((size_t)P.hq * nb * P.hist_words * 4);
+    w.cpart = take(evisel::coarse_part_floats((int)P.tiles.size(), P.hq,
+                                              P.hist_words) * 4);
+  } else {
+    w.kbar = w.rbits = w.ubits = w.cpart = 0;
+  }
+  w.total = off;
+  const int fpt = P.layout.Nv >= 1 && 64 % P.layout.Nv == 0
+                      ? 64 / P.layout.Nv : 1;
+  w.segv = take((size_t)P.hq * P.col.size() * fpt * 64 * 4);
+  w.lse2v = take((size_t)P.hq * P.S * 4);
+  w.intra_part = take((size_t)P.hkv * P.T * P.layout.Nv * P.layout.Nv * 4);
+  w.cue_total = off - w.total;
+  return w;
+}
+
 evisel_status make_plan(const evisel_layout* layout,
                         const evisel_mask_rule* rule, int32_t hq, int32_t hkv,
                         evisel_mask** out, evisel_mask** made) {
@@ -70,6 +110,12 @@ evisel_status make_plan(const evisel_layout* layout,
   std::string err;
   try {
     err = evisel::build_plan(L, R, hq, hkv, &m->plan);
+    // short chunks must not take a mask past the static workspace
+    if (err.empty() && m->plan.chunk_blocks < evisel::kChunkBlocks) {
+      const WsLayout w = ws_layout(m->plan, 128);
+      if (w.total + w.cue_total > EVISEL_NOALLOC_WORKSPACE_BYTES)
+        err = evisel::build_plan(L, R, hq, hkv, &m->plan, false);
+    }
   } catch (const std::bad_alloc&) {
     delete m;
     return fail(EVISEL_ERR_NOMEM, "host allocation failed");
@@ -181,46 +227,6 @@ evisel_status upload(evisel_mask* m, hipStream_t s) {
   for (const auto& sq : P.seqs)
     dp.max_frames = std::max(dp.max_frames, sq.n_frames);
   return EVISEL_OK;
-}
-
-struct WsLayout {
-  size_t pO, pM, pL, pNV, seg, kbar, rbits, ubits, cpart, total;
-  size_t segv, lse2v, intra_part, cue_total;   // frame cues, after `total`
-};
-
-WsLayout ws_layout(const evisel::Plan& P, int32_t d) {
-  WsLayout w{};
-  size_t off = 0;
-  auto take = [&](size_t bytes) {
-    const size_t o = off;
-    off += align256(bytes);
-    return o;
-  };
-  const size_t rows = (size_t)P.n_slots * 64;
-  w.pO = take(rows * d * 4);
-  w.pM = take(rows * 4);
-  w.pL = take(rows * 4);
-  w.pNV = take(rows * 4);
-  w.seg = take((size_t)P.hq * P.segtot * 4);
-  if (P.rule.tau > 0.f) {
-    const size_t nb = P.blocks.size();
-    // bf16 keeps hi and lo (2 x 2 bytes), fp32 one float: 4 bytes either way
-    w.kbar = take((size_t)P.hkv * nb * d * 4);
-    w.rbits = take((size_t)P.hq * nb * P.hist_words * 64 * 4);
-    w.ubits = take((size_t)P.hq * nb * P.hist_words * 4);
-    w.cpart = take(evisel::coarse_part_floats((int)P.tiles.size(), P.hq,
-                                              P.hist_words) * 4);
-  } else {
-    w.kbar = w.rbits = w.ubits = w.cpart = 0;
-  }
-  w.total = off;
-  const int fpt = P.layout.Nv >= 1 && 64 % P.layout.Nv == 0
-                      ? 64 / P.layout.Nv : 1;
-  w.segv = take((size_t)P.hq * P.col.size() * fpt * 64 * 4);
-  w.lse2v = take((size_t)P.hq * P.S * 4);
-  w.intra_part = take((size_t)P.hkv * P.T * P.layout.Nv * P.layout.Nv * 4);
-  w.cue_total = off - w.total;
-  return w;
 }
 
 bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }

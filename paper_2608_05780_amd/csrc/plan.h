@@ -142,12 +142,16 @@ struct Plan {
   std::vector<int32_t> ff_out_ptr, ff_out_idx, ff_in_ptr, ff_in_idx;
 };
 
-// Builds the plan; returns "" on success or an error message.
+// Builds the plan; returns "" on success or an error message. short_chunks:
+// the split query-token rows of small masks may go below kChunkBlocks key
+// blocks per chunk (more partials, so more workspace).
 std::string build_plan(const Layout& layout, const Rule& rule, int32_t hq,
-                       int32_t hkv, Plan* out);
+                       int32_t hkv, Plan* out, bool short_chunks = true);
 
 // Number of hardware queues the launch order interleaves (one per XCD).
 constexpr int kXcds = 8;
+// Key blocks a chunk of a split query-token row holds at least (larger masks).
+constexpr int kChunkBlocks = 16;
 // Concurrent work items the split heuristic aims to fill (256 CUs x 1).
 constexpr int kTargetSlots = 512;
 
