@@ -1,8 +1,8 @@
-// Software-pipelined block-sparse prefill attention for gfx950 (bf16 inputs,
-// static sparse rule, no frame-cue outputs) with the fused query-frame
-// evidence partials. Same work items, LDS tile layout, loaders and outputs
-// as attn_kernel (attn.hip); what differs is the order of work inside a
-// wavefront.
+// Software-pipelined block-sparse prefill attention for gfx950 (bf16 inputs;
+// static sparse rule, with or without frame-cue outputs, or top-p retention
+// without them) with the fused query-frame evidence partials. Same work
+// items, LDS tile layout, loaders and outputs as attn_kernel (attn.hip); what
+// differs is the order of work inside a wavefront.
 //
 // A wave (32 query rows of one head) keeps its MFMA pipe busy by running the
 // VALU work of one tile beside the MFMAs of another. Per loop iteration j:
@@ -24,6 +24,14 @@
 // again by a plain per-tile exact loop (row max per tile, lazy rescale),
 // which rewrites every output the first pass wrote. On ordinary inputs no
 // row's logits rise 64 log2 units above its first tile's.
+//
+// Top-p form: the item's candidate tiles are compacted first, as in
+// attn_kernel, and a row that did not retain a history tile takes its
+// probabilities against +inf (all 0). Its reference may then come from a tile
+// it did not keep: a row whose sum ends below 2^-64 marks the wave too, and a
+// query row that kept none of the item's tiles leaves an empty partial. 256
+// frames x 64 tokens + 128 query tokens, 28/4 heads, d = 128, rows that keep
+// 45 % of their history: the layer takes 1,907 us, 1,993 with attn_kernel.
 //
 // LDS: [K0 | K1 | V0 | V1], one 64-key tile each, as attn_kernel. Key tile
 // t lives in K(t % 2) and value tile t in V(t % 2); K(j+2) and V(j+1) are
@@ -67,6 +75,13 @@ struct PipeArgs {
   float* segv;
   float* lse2v;
   int32_t nnz;
+  // top-p retention (the kernel's TOPP form): per-row and per-block bits,
+  // and what tells a candidate tile's local history index
+  const int32_t* col;
+  const int32_t* blk_local;
+  const uint32_t* rbits;
+  const uint32_t* ubits;
+  int32_t nb, W;
 };
 
 // A key tile as the loop sees it (wave-uniform).
@@ -74,6 +89,7 @@ struct Tile {
   int start, len, region, aux;
   bool act;   // some row of this wave's half attends to it
   int pos;    // CSR position of the tile for this half (CUE form only)
+  int loc;    // local history index, -1: always visible (TOPP form only)
 };
 
 // Instruction order requested from the scheduler (sched_group_barrier
@@ -130,10 +146,8 @@ __device__ __forceinline__ void sched_block2() {
   }
 }
 
-template <int D, bool CUE>
-__global__ __attribute__((amdgpu_flat_work_group_size(kThreads, kThreads),
-                          amdgpu_waves_per_eu(2, 2))) void
-attn_pipe_kernel(const PipeArgs a) {
+template <int D, bool CUE, bool TOPP>
+__device__ __forceinline__ void attn_pipe_item(const PipeArgs a) {
   using P = Bf16Path<D>;
   constexpr int RC = P::RC;             // 16-byte chunks per row
   constexpr int TB = kTile * RC * 16;   // bytes of one tile
@@ -143,9 +157,13 @@ attn_pipe_kernel(const PipeArgs a) {
   EV_LDS char* const kb0 = (EV_LDS char*)smem;   // [K0 | K1 | V0 | V1]
   EV_LDS char* const vb0 = kb0 + 2 * TB;
 
+  // top-p: positions in the item's run of the key tiles some row retained
+  __shared__ short clist[TOPP ? kMaxItemCandidates : 1];
+  __shared__ int n_kept;
+
   const WorkItem it = a.items[blockIdx.x];
   if (it.qblock < 0) return;
-  const int n = it.kb_end - it.kb_begin;   // key tiles of the item
+  int n = it.kb_end - it.kb_begin;   // key tiles of the item
   if (n <= 0) return;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -167,18 +185,36 @@ attn_pipe_kernel(const PipeArgs a) {
   const int b0 = it.kb_begin;
   const float c2 = a.c2;
 
+  // Whether some row of block `own`, heads head .. head + nh - 1, retained
+  // history block loc.
+  auto block_kept = [&](int own, int nh, int loc) {
+    const uint32_t* w =
+        a.ubits + ((size_t)it.head * a.nb + own) * a.W + (loc >> 5);
+    unsigned wd = w[0];
+    if (nh > 1) wd |= w[(size_t)a.nb * a.W];
+    return ((wd >> (loc & 31)) & 1u) != 0u;
+  };
   // Tile descriptors, 64 at a time: lane t holds tile 64 * batch + t's
-  // first token, aux field and (length | region << 8 | active << 10).
+  // first token, aux field and (length | region << 8 | active << 10); top-p:
+  // local history index + 1 from bit 11 (0: always visible).
   int dsc_start = 0, dsc_aux = 0, dsc_meta = 1, dsc_pos = -1;
   auto load_batch = [&](int batch) {
     const int t = batch * 64 + lane;
     if (t < n) {
-      const BlockDesc bd = uni ? a.ptile_desc[b0 + t] : a.col_desc[b0 + t];
-      const int act = uni ? (a.ptile[b0 + t].pos[hsub] >= 0 ? 1 : 0) : 1;
+      const int p = b0 + (TOPP ? (int)clist[t] : t);
+      const BlockDesc bd = uni ? a.ptile_desc[p] : a.col_desc[p];
+      int act = uni ? (a.ptile[p].pos[hsub] >= 0 ? 1 : 0) : 1;
       dsc_start = bd.start;
       dsc_aux = bd.aux;
-      dsc_meta = bd.len | bd.region << 8 | act << 10;
-      if (CUE) dsc_pos = uni ? a.ptile[b0 + t].pos[hsub] : b0 + t;
+      if (CUE) dsc_pos = uni ? a.ptile[p].pos[hsub] : p;
+      int loc1 = 0;
+      if (TOPP) {
+        const int bid = uni ? a.ptile[p].block : a.col[p];
+        if (bid != qbid) loc1 = a.blk_local[bid] + 1;
+        // half of a paired item: a history block none of its rows retained
+        if (uni && act && loc1 > 0 && !block_kept(qbid, 1, loc1 - 1)) act = 0;
+      }
+      dsc_meta = bd.len | bd.region << 8 | act << 10 | loc1 << 11;
     }
   };
   auto desc = [&](int t) {
@@ -191,9 +227,19 @@ attn_pipe_kernel(const PipeArgs a) {
     d.region = (meta >> 8) & 3;
     d.act = (meta >> 10) & 1;
     d.pos = CUE ? __builtin_amdgcn_readlane(dsc_pos, l) : -1;
+    d.loc = TOPP ? (meta >> 11) - 1 : -1;
     return d;
   };
-  const Tile none = {0, 1, 0, 0, false, -1};
+  const Tile none = {0, 1, 0, 0, false, -1, -1};
+  // The word of the row's retained-history bits that covers tile t.
+  const uint32_t* const rbase =
+      TOPP ? a.rbits + ((size_t)h * a.nb + qbid) * a.W * 64 : nullptr;
+  auto row_word = [&](const Tile& t) -> unsigned {
+    return t.loc < 0 ? ~0u : rbase[(t.loc >> 5) * 64 + qrow];
+  };
+  auto row_keeps = [&](const Tile& t, unsigned w) -> bool {
+    return !TOPP || t.loc < 0 || ((w >> (t.loc & 31)) & 1u);
+  };
 
   TileLoader<__bf16, D, kSwzK> kload;
   TileLoader<__bf16, D, kSwzV> vload;
@@ -204,8 +250,9 @@ attn_pipe_kernel(const PipeArgs a) {
 
   // Prologue: descriptors, both halves' query rows (staged in K1 and V1)
   // and key/value tile 0 in one round trip; key tile 1 follows once the
-  // query rows are in registers.
-  load_batch(0);
+  // query rows are in registers. Top-p: wave 0 first compacts the candidate
+  // tiles that some row of the item needs, while the query rows arrive.
+  if (!TOPP) load_batch(0);
   {
     TileLoader<__bf16, D, kSwzK> qload;
     qload.init(a.hq, wave, lane);
@@ -213,14 +260,62 @@ attn_pipe_kernel(const PipeArgs a) {
     if (nhalf > 1)
       qload.issue(vb0 + TB, a.q, it.q1start, it.q1len, hd1, wave);
   }
-  kload.issue(kb0, a.k, it.k0start, it.k0len, kvh, wave);
-  vload.issue(vb0, a.v, it.k0start, it.k0len, kvh, wave);
+  int k0start = it.k0start, k0len = it.k0len;
+  if constexpr (TOPP) {
+    if (wave == 0) {
+      int base = 0;
+      for (int c0 = 0; c0 < n; c0 += 64) {
+        const int t = c0 + lane;
+        bool keep = false;
+        if (t < n && uni) {
+          // paired item: kept when either half's rows need it
+          const PairedTile pt = a.ptile[b0 + t];
+          const int loc = a.blk_local[pt.block];
+          keep = (pt.pos[0] >= 0 && (loc < 0 || pt.block == it.qblock ||
+                                     block_kept(it.qblock, 1, loc))) ||
+                 (pt.pos[1] >= 0 && (loc < 0 || pt.block == it.qblock2 ||
+                                     block_kept(it.qblock2, 1, loc)));
+        } else if (t < n) {
+          const int bid = a.col[b0 + t];
+          const int loc = a.blk_local[bid];
+          keep = loc < 0 || bid == it.qblock ||
+                 block_kept(it.qblock, it.nheads, loc);
+        }
+        const unsigned long long m = __ballot(keep);
+        const int pos = __builtin_amdgcn_mbcnt_hi(
+            (unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
+        if (keep) clist[base + pos] = (short)t;
+        base += __popcll(m);
+      }
+      if (lane == 0) n_kept = base;
+    }
+    __syncthreads();
+    n = __builtin_amdgcn_readfirstlane(n_kept);
+    if (n > 0) {
+      load_batch(0);
+      const Tile t0 = desc(0);
+      k0start = t0.start;
+      k0len = t0.len;
+    }
+  }
+  if (!TOPP || n > 0) {
+    kload.issue(kb0, a.k, k0start, k0len, kvh, wave);
+    vload.issue(vb0, a.v, k0start, k0len, kvh, wave);
+  }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
   typename P::QFrag qf;
   P::load_q_lds(qf, hsub ? vb0 + TB : kb0 + TB, qrow, g);
   __syncthreads();   // every wave has its query rows: K1 and V1 are free
-  if (n > 1) kload.issue(kb0 + TB, a.k, it.k1start, it.k1len, kvh, wave);
+  if (n > 1) {
+    int k1start = it.k1start, k1len = it.k1len;
+    if (TOPP) {
+      const Tile t1 = desc(1);
+      k1start = t1.start;
+      k1len = t1.len;
+    }
+    kload.issue(kb0 + TB, a.k, k1start, k1len, kvh, wave);
+  }
 
   // query-token rows: this video's offsets
   SeqDesc sq{};
@@ -388,10 +483,10 @@ attn_pipe_kernel(const PipeArgs a) {
 #pragma unroll
     for (int i = 0; i < NMT; ++i) o[i] = f32x16{};
     load_batch(0);
-    kload.issue(kb0, a.k, it.k0start, it.k0len, kvh, wave);
-    vload.issue(vb0, a.v, it.k0start, it.k0len, kvh, wave);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     Tile cur = desc(0);
+    kload.issue(kb0, a.k, cur.start, cur.len, kvh, wave);
+    vload.issue(vb0, a.v, cur.start, cur.len, kvh, wave);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     for (int t = 0; t < n; ++t) {
       if (t + 1 < n && ((t + 1) & 63) == 0) load_batch((t + 1) >> 6);
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -410,6 +505,10 @@ attn_pipe_kernel(const PipeArgs a) {
         if (need_mask(cur)) {
           mask_half(s[0], 0, cur);
           mask_half(s[1], 1, cur);
+        }
+        if (TOPP && !row_keeps(cur, row_word(cur))) {
+#pragma unroll
+          for (int r = 0; r < 16; ++r) s[0][r] = s[1][r] = neg_inf();
         }
         float mx = neg_inf();
 #pragma unroll
@@ -472,6 +571,10 @@ attn_pipe_kernel(const PipeArgs a) {
     bf16x8 pb[4];
     float th = 0.f;   // fp32 sum of the probabilities of keys 0-31
     bool started = false, bad = false;
+    // top-p: rows of the lane that keep tile j (keep_c) and j + 1 (keep_n), the bits'
+    // word of tile j + 2, and whether the row kept any tile
+    bool keep_c = true, keep_n = true, kany = !TOPP;
+    unsigned wnn = ~0u;
     const float pinf = __builtin_inff();
 
     // keys 0-31 of a tile (logits in s0) to pb[0..1] and their sum
@@ -505,7 +608,12 @@ attn_pipe_kernel(const PipeArgs a) {
     qk_half(s1, kb0, 1);
     if (need_mask(tn)) mask_half(s0, 0, tn);
     if (active && tn.act) first_tile(tn);
-    start_half(tn.act && started ? m_ref : pinf);
+    if (TOPP) {
+      keep_n = row_keeps(tn, row_word(tn));
+      if (n > 1) wnn = row_word(tnn);
+      kany = tn.act && keep_n;
+    }
+    start_half(tn.act && started && keep_n ? m_ref : pinf);
 
     // top of iteration j: key tile j+1 and value tile j have landed; every
     // wave is past iteration j-1, so K(j % 2) and V((j+1) % 2) may be
@@ -516,7 +624,13 @@ attn_pipe_kernel(const PipeArgs a) {
       __syncthreads();
       tc = tn;
       tn = tnn;
+      if (TOPP) {
+        keep_c = keep_n;
+        keep_n = row_keeps(tn, wnn);
+        kany = kany || (j + 1 < n && tn.act && keep_n);
+      }
       tnn = j + 2 < n ? desc(j + 2) : none;
+      if (TOPP && j + 2 < n) wnn = row_word(tnn);
       if (j + 2 < n)
         kload.issue(kb0 + (j & 1) * TB, a.k, tnn.start, tnn.len, kvh, wave);
       if (j + 1 < n)
@@ -531,7 +645,7 @@ attn_pipe_kernel(const PipeArgs a) {
       const EV_LDS char* const vc = vb0 + pj * TB;   // value tile j
       top(j);
       const Tile cur = tc, nxt = tn;
-      const float mu_c = cur.act ? m_ref : pinf;
+      const float mu_c = cur.act && keep_c ? m_ref : pinf;
       if (need_mask(cur)) mask_half(s1, 1, cur);
       // block 1: QK(j+1) beside the exponentials of tile j, keys 32-63.
       // The 16 K operand reads run four ahead of their MFMAs; the first
@@ -557,7 +671,7 @@ attn_pipe_kernel(const PipeArgs a) {
       }
       if (need_mask(nxt)) mask_half(s0, 0, nxt);
       if (!started && active && nxt.act) first_tile(nxt);
-      const float mu_n = nxt.act && started ? m_ref : pinf;
+      const float mu_n = nxt.act && started && keep_n ? m_ref : pinf;
       // block 2: PV(j) beside the exponentials of tile j+1, keys 0-31,
       // which replace pb[0..1] once the PV MFMAs have read them. The V^T
       // operand reads (two per MFMA) run four MFMAs ahead.
@@ -591,8 +705,16 @@ attn_pipe_kernel(const PipeArgs a) {
     {
       const Tile cur = tc;
       if (need_mask(cur)) mask_half(s1, 1, cur);
-      finish(cur, soft_half(s1, pb[2], pb[3], cur.act ? m_ref : pinf));
+      finish(cur, soft_half(s1, pb[2], pb[3], cur.act && keep_c ? m_ref : pinf));
       pv_tile(vb0 + (j & 1) * TB, pb);
+    }
+    if (TOPP) {
+      // The reference comes from a tile the row may not have kept: a row
+      // whose own keys all lie far below it is computed again. A row that
+      // kept none of the item's tiles leaves an empty partial.
+      const float lt = pair_sum(l_part);
+      bad = bad || __any(qvalid && kany && !(lt >= 1.f / kFastBound));
+      if (!kany) m_ref = neg_inf();
     }
     // votes, in V0 (the O rows are staged in K0 and K1 afterwards): every
     // wave is done with the tiles
@@ -610,7 +732,9 @@ attn_pipe_kernel(const PipeArgs a) {
   // The "top" of the first iteration is the prologue's wait and barrier: the
   // loop driver's top(j) runs from j = 0 and expects tile descriptors 0 and
   // 1 in tn / tnn before iteration -1, which sets them up itself.
-  if (!is_text) {
+  if (TOPP && n == 0) {
+    // (a chunk of a query row none of whose tiles was kept: an empty partial)
+  } else if (!is_text) {
     pipeline(std::false_type{});
   } else if (a.Nv >= 32) {
     pipeline(std::true_type{});
@@ -658,12 +782,27 @@ attn_pipe_kernel(const PipeArgs a) {
   }
 }
 
+template <int D, bool CUE>
+__global__ __attribute__((amdgpu_flat_work_group_size(kThreads, kThreads),
+                          amdgpu_waves_per_eu(2, 2))) void
+attn_pipe_kernel(const PipeArgs a) {
+  attn_pipe_item<D, CUE, false>(a);
+}
+
+template <int D>
+__global__ __attribute__((amdgpu_flat_work_group_size(kThreads, kThreads),
+                          amdgpu_waves_per_eu(2, 2))) void
+attn_pipe_topp_kernel(const PipeArgs a) {
+  attn_pipe_item<D, false, true>(a);
+}
+
 }  // namespace
 
 bool attention_pipe_supported(const DevPlan& p, const AttnCall& c) {
-  // frame cues: frames of 32 or 64 keys (the loop keeps two half-tile sums)
+  // frame cues: frames of 32 or 64 keys (the loop keeps two half-tile sums),
+  // and not with top-p (the two forms together run out of registers)
   const bool cues = c.segv != nullptr || c.lse2v != nullptr;
-  return !c.fp32 && !p.topp && (!cues || p.Nv >= 32) &&
+  return !c.fp32 && (!cues || (p.Nv >= 32 && !p.topp)) &&
          (c.d == 64 || c.d == 128);
 }
 
@@ -696,9 +835,20 @@ hipError_t launch_attention_pipe(const DevPlan& p, const Workspace& w,
   a.segv = c.segv;
   a.lse2v = c.lse2v;
   a.nnz = p.nnz;
+  a.col = p.col;
+  a.blk_local = p.blk_local;
+  a.rbits = w.rbits;
+  a.ubits = w.ubits;
+  a.nb = p.nb;
+  a.W = p.W;
   const bool cue = c.segv != nullptr || c.lse2v != nullptr;
   dim3 grid(p.n_items), block(kThreads);
-  if (c.d == 64 && cue)
+  if (p.topp) {
+    if (c.d == 64)
+      attn_pipe_topp_kernel<64><<<grid, block, 0, s>>>(a);
+    else
+      attn_pipe_topp_kernel<128><<<grid, block, 0, s>>>(a);
+  } else if (c.d == 64 && cue)
     attn_pipe_kernel<64, true><<<grid, block, 0, s>>>(a);
   else if (c.d == 64)
     attn_pipe_kernel<64, false><<<grid, block, 0, s>>>(a);

@@ -82,8 +82,9 @@ struct AttnCall {
 hipError_t launch_attention(const DevPlan& p, const Workspace& w,
                             const AttnCall& c, hipStream_t s);
 // The software-pipelined attention kernel (attn_pipe.hip): bf16, d = 64 or
-// 128, static rule, no frame-cue outputs; launch_attention uses it for
-// every call it supports.
+// 128, without frame-cue outputs, or with them under the static rule and
+// frames of 32 or 64 tokens; launch_attention uses it for every call it
+// supports.
 bool attention_pipe_supported(const DevPlan& p, const AttnCall& c);
 hipError_t launch_attention_pipe(const DevPlan& p, const Workspace& w,
                                  const AttnCall& c, hipStream_t s);
