@@ -136,9 +136,6 @@ __device__ __forceinline__ int grp_sumi(int x) {
   x += dpp<kQuadSwap2>(x);
   if (TPR >= 8) x += dpp<kHalfMirror>(x);
   if (TPR >= 16) x += dpp<kRowMirror>(x);
-  if (TPR >= 64)
-    x = (int)cross_rows((unsigned)x,
-                        [](unsigned a, unsigned b) { return a + b; });
   return x;
 }
 template <int TPR>
@@ -169,8 +166,6 @@ __device__ __forceinline__ unsigned grp_maxu(unsigned x) {
   x = max(x, (unsigned)dpp<kQuadSwap2>((int)x));
   if (TPR >= 8) x = max(x, (unsigned)dpp<kHalfMirror>((int)x));
   if (TPR >= 16) x = max(x, (unsigned)dpp<kRowMirror>((int)x));
-  if (TPR >= 64)
-    x = cross_rows(x, [](unsigned a, unsigned b) { return max(a, b); });
   return x;
 }
 
@@ -198,9 +193,7 @@ inline size_t sel_lds_bytes(int nh_max, int tpr, int W, int d) {
 // LDS, entries [j0, j0 + cnt) of the row's history at my[0 .. cnt). Sets the
 // retained history bits in wrow (LDS, OR). retain_row_regs keeps the lane's
 // L <= RV values in registers (RV = kRegVals, or kRegValsLong for the long
-// form), retain_row_lds streams them from LDS. retain_regs is the register
-// form itself: it leaves e_j in v, the lane's retained bits in mw and the
-// row's largest g in mx, for a caller that goes on with them.
+// form), retain_row_lds streams them from LDS.
 // Both find the same cut except where a tail sum F lies within its fp32
 // rounding of the threshold (they associate the sums differently).
 //
@@ -289,19 +282,19 @@ __device__ __forceinline__ void tie_share(int mine, float fhi, float thr,
   }
 }
 
-template <int TPR, int RV, int NW>
-__device__ __forceinline__ void retain_regs(float* my, int L, int nh,
-                                            float tau, int lane, int part,
-                                            float (&v)[RV],
-                                            unsigned (&mw)[NW], float& mx) {
+template <int TPR, int RV>
+__device__ __forceinline__ void retain_row_regs(float* my, int L, int nh,
+                                                int j0, float tau, int lane,
+                                                int part, uint32_t* wrow) {
   constexpr int NCK = RV / 4;
-  static_assert(NW == (RV + 31) / 32, "mask words");
+  constexpr int NW = (RV + 31) / 32;   // mask words
   const int nck = L >> 2;                         // uniform per work-group
   // Entries past the history hold -inf (the affinity pass writes the row
   // up to TPR * L), so their e is +0; the cut t* found below is never 0 (F
   // at any key up to the smallest positive e is the whole sum Z >= tau Z),
   // so zeros are never retained or counted as ties, and no validity mask
   // is needed.
+  float v[RV];
 #pragma unroll
   for (int c = 0; c < NCK; ++c) {
     f32x4 t = {};
@@ -310,7 +303,7 @@ __device__ __forceinline__ void retain_regs(float* my, int L, int nh,
     for (int e = 0; e < 4; ++e) v[4 * c + e] = t[e];
   }
   // (chunks c >= nck hold no entries: skipped, and +0 from here on)
-  mx = neg_inf();
+  float mx = neg_inf();
 #pragma unroll
   for (int c = 0; c < NCK; ++c)
     if (c < nck)
@@ -422,6 +415,7 @@ __device__ __forceinline__ void retain_regs(float* my, int L, int nh,
       }
     }
   }
+  unsigned mw[NW];
 #pragma unroll
   for (int k = 0; k < NW; ++k) mw[k] = 0u;
   if (clo - chi <= 1) {
@@ -451,16 +445,6 @@ __device__ __forceinline__ void retain_regs(float* my, int L, int nh,
       mw[i >> 5] |= sel ? 1u << (i & 31) : 0u;
     }
   }
-}
-
-template <int TPR, int RV>
-__device__ __forceinline__ void retain_row_regs(float* my, int L, int nh,
-                                                int j0, float tau, int lane,
-                                                int part, uint32_t* wrow) {
-  constexpr int NW = (RV + 31) / 32;
-  float v[RV], mx;
-  unsigned mw[NW];
-  retain_regs<TPR, RV, NW>(my, L, nh, tau, lane, part, v, mw, mx);
   or_bits_w<NW>(wrow, j0, mw);
 }
 
@@ -561,13 +545,14 @@ __device__ __forceinline__ void store_affinities(const f32x16& acc, float sc,
 // first + j), written to ev[rl * stride + j]; columns nh <= j < ncols
 // (ncols <= stride) get -inf. A wave takes the 32-row group rg and every
 // wpg-th 32-column tile from ph: S^T = Kbar Q^T on bf16 MFMA with kbar =
-// hi + lo accumulated into one fp32 tile (fp32: 32x32x2 MFMA).
+// hi + lo accumulated into one fp32 tile (fp32: 32x32x2 MFMA). bf16: qs holds
+// the rows, staged in LDS, and the whole work-group takes part.
 template <bool F32, int D>
 __device__ __forceinline__ void affinity_tiles(
     const DevPlan& pl, const void* kbar, const void* q, float scale_log2,
     const BlockDesc& qb, int h, int kvh, int first, int nh, int ncols,
     int r0, int rows, int rg, int ph, int wpg, float* ev, int stride,
-    int lane, const __bf16* qs = nullptr) {
+    int lane, const __bf16* qs) {
   const int l32 = lane & 31, g = lane >> 5;
   const int ntile = (ncols + 31) / 32;
   const int rl = rg * 32 + l32;
@@ -577,20 +562,12 @@ __device__ __forceinline__ void affinity_tiles(
   const size_t qoff = ((size_t)(qb.start + (rv ? r0 + rl : 0)) * pl.hq + h) * D;
   if (!F32) {
     bf16x8 qf[D / 16];
-    if (qs) {
-      // rows staged in LDS by the whole work-group ([rows][D + 8]); every
-      // wave has its operands before the first affinity overwrites them
-      const __bf16* qr = qs + min(rl, rows - 1) * (D + 8) + 8 * g;
+    // rows staged in LDS by the whole work-group ([rows][D + 8]); every wave
+    // has its operands before the first affinity overwrites them
+    const __bf16* qr = qs + min(rl, rows - 1) * (D + 8) + 8 * g;
 #pragma unroll
-      for (int kk = 0; kk < D / 16; ++kk)
-        qf[kk] = *(const bf16x8*)(qr + 16 * kk);
-      __syncthreads();
-    } else {
-      const __bf16* qg = (const __bf16*)q + qoff + 8 * g;
-#pragma unroll
-      for (int kk = 0; kk < D / 16; ++kk)
-        qf[kk] = *(const bf16x8*)(qg + 16 * kk);
-    }
+    for (int kk = 0; kk < D / 16; ++kk) qf[kk] = *(const bf16x8*)(qr + 16 * kk);
+    __syncthreads();
     // chunk 2 kk + g of block first + jb (d-chunk-major layout)
     const __bf16* kh0 = (const __bf16*)kbar +
                         (((size_t)kvh * (D / 8) + g) * pl.nb + first) * 8;
@@ -773,23 +750,31 @@ __global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(
 // and the retained values are still in registers when the masses are formed.
 // coarse_kernel takes one query-token block, one head and one pass of 16
 // rows, one wavefront per row (any history the mask accepts then fits a
-// lane's kRegVals registers). The grid is small (a few hundred work-groups
-// whatever the history), so latency bounds it: 16 waves share a work-group's
-// affinity tiles and every row is searched at once. The whole call (means,
-// this kernel, the reduction) takes 33 us on 256 frames x 64 tokens + 128
-// query tokens and 48 us on 1,024 frames (28/4 heads, d = 128, bf16),
-// against 183 us and 3.6 ms when the retention of every row was decided
-// first. The per-block masses of the pass's rows are summed in row order
+// lane's registers). The grid is small (a few hundred work-groups whatever
+// the history), so latency bounds it: 16 waves share a work-group's
+// affinity tiles and every row is searched at once, its bounds in scalar
+// registers. The whole call (means, this kernel, the reduction) takes 25.5 us
+// on 256 frames x 64 tokens + 128 query tokens and 44.1 us on 1,024 frames
+// (28/4 heads, d = 128, bf16), against 183 us and 3.6 ms when the retention
+// of every row was decided first (30.4 and 46.7 us with the lane-group search
+// of select_kernel on 64 lanes). The per-block masses of the pass's rows are summed in row order
 // into cpart; coarse_reduce_kernel adds a video's blocks and passes in order
 // and spreads each block's mass evenly over its frames (frames never cross
 // blocks).
-constexpr int kCoarseTPR = 64;
 constexpr int kCoarseThreads = 1024;
 constexpr int kCoarseWaves = kCoarseThreads / 64;
-constexpr int kCoarseRows = kCoarseThreads / kCoarseTPR;   // rows per pass
+constexpr int kCoarseRows = kCoarseWaves;                  // rows per pass
+constexpr int kCoarseVals = 32;                            // blocks per lane
 constexpr int kCoarsePasses = kTile64 / kCoarseRows;
-static_assert(kMaxItemCandidates <= kCoarseTPR * kRegVals,
+// The last waves take the E_i tiles, the others the affinity tiles.
+constexpr int kCoarseExact = 2;
+constexpr int kCoarseAff = kCoarseWaves - kCoarseExact;
+static_assert(kMaxItemCandidates <= 64 * kCoarseVals,
               "a row's share of the longest history fits its registers");
+// LDS floats of a row: its history in tiles of 16, and a bank offset.
+__host__ __device__ inline int coarse_stride(int nh) {
+  return ((nh + 15) & ~15) + 4;
+}
 
 __device__ __forceinline__ float pair_max_(float x) {
   auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x),
@@ -803,11 +788,10 @@ __device__ __forceinline__ float pair_sum_(float x) {
 }
 
 // Log2 max and sum of row r0 + l32's exact logits over the E_i tiles e =
-// ph, ph + kCoarseWaves, ... (system-prefix blocks, then the row's own block).
+// ph, ph + kCoarseExact, ... (system-prefix blocks, then the row's own block).
 template <bool F32, int D>
 __device__ __forceinline__ void exact_part(
-    const DevPlan& pl, const SelCall& sc, const BlockDesc& qb, int qbid,
-    int h, int kvh, int sys0, int nsys, int r0, int ph, int lane, float& mw,
+    const DevPlan& pl, const SelCall& sc, const BlockDesc& qb, int h, int kvh, int sys0, int nsys, int r0, int ph, int lane, float& mw,
     float& lw) {
   const int l32 = lane & 31, g = lane >> 5;
   const bool rv = l32 < kCoarseRows && r0 + l32 < qb.len;
@@ -815,29 +799,49 @@ __device__ __forceinline__ void exact_part(
   const size_t qoff = ((size_t)(rv ? qtok : qb.start) * pl.hq + h) * D;
   mw = -__builtin_inff();
   lw = 0.f;
-  for (int e = ph; e <= nsys; e += kCoarseWaves) {
-    const int kbid = e < nsys ? sys0 + e : qbid;
-    const BlockDesc kb = pl.blocks[kbid];
+  for (int e = ph; e <= nsys; e += kCoarseExact) {
+    const BlockDesc kb = e < nsys ? pl.blocks[sys0 + e] : qb;
     f32x16 s[2] = {f32x16{}, f32x16{}};
+    const int key0 = min(l32, kb.len - 1), key1 = min(32 + l32, kb.len - 1);
+    const size_t ko0 = ((size_t)(kb.start + key0) * pl.hkv + kvh) * D;
+    const size_t ko1 = ((size_t)(kb.start + key1) * pl.hkv + kvh) * D;
+    if (!F32) {
+      // both halves' operands in flight at once (one round trip to memory)
+      constexpr int KS = D / 16;
+      const __bf16* const ks = (const __bf16*)sc.k + 8 * g;
+      const __bf16* const qs = (const __bf16*)sc.q + qoff + 8 * g;
+      bf16x8 qf[KS], k0[KS], k1[KS];
 #pragma unroll
-    for (int c = 0; c < 2; ++c) {
-      const int key = min(32 * c + l32, kb.len - 1);
-      const size_t koff = ((size_t)(kb.start + key) * pl.hkv + kvh) * D;
-      if (!F32) {
-        const __bf16* ks = (const __bf16*)sc.k + koff + 8 * g;
-        const __bf16* qs = (const __bf16*)sc.q + qoff + 8 * g;
+      for (int kk = 0; kk < KS; ++kk) {
+        qf[kk] = *(const bf16x8*)(qs + 16 * kk);
+        k0[kk] = *(const bf16x8*)(ks + ko0 + 16 * kk);
+      }
 #pragma unroll
-        for (int kk = 0; kk < D / 16; ++kk)
-          s[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-              *(const bf16x8*)(ks + 16 * kk), *(const bf16x8*)(qs + 16 * kk),
-              s[c], 0, 0, 0);
-      } else {
-        const float* ks = (const float*)sc.k + koff + g * (D / 2);
-        const float* qs = (const float*)sc.q + qoff + g * (D / 2);
+      for (int kk = 0; kk < KS; ++kk)
+        k1[kk] = *(const bf16x8*)(ks + ko1 + 16 * kk);
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int u = 0; u < D / 2; ++u)
-          s[c] = __builtin_amdgcn_mfma_f32_32x32x2f32(ks[u], qs[u], s[c], 0, 0,
+      for (int kk = 0; kk < KS; ++kk) {
+        s[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k0[kk], qf[kk], s[0], 0,
+                                                       0, 0);
+        s[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k1[kk], qf[kk], s[1], 0,
+                                                       0, 0);
+      }
+    } else {
+      const float* const ks = (const float*)sc.k + g * (D / 2);
+      const float* const qs = (const float*)sc.q + qoff + g * (D / 2);
+#pragma unroll
+      for (int u = 0; u < D / 8; ++u) {
+        const f32x4 qv = *(const f32x4*)(qs + 4 * u);
+        const f32x4 a = *(const f32x4*)(ks + ko0 + 4 * u);
+        const f32x4 b = *(const f32x4*)(ks + ko1 + 4 * u);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          s[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[e], qv[e], s[0], 0, 0,
                                                       0);
+          s[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(b[e], qv[e], s[1], 0, 0,
+                                                      0);
+        }
       }
     }
     float mt = -__builtin_inff();
@@ -865,12 +869,66 @@ __device__ __forceinline__ void exact_part(
   }
 }
 
+// Affinities of the pass's 16 query rows (bf16) against history blocks
+// 16 t .. 16 t + 15 for t = wave, wave + kCoarseAff, ..., to ev[row * stride +
+// block] (blocks past the history get -inf): 16x16x32 MFMA, kbar = hi + lo, the
+// next tile's operands in flight while one is multiplied. The first tile's
+// come with the query rows.
+template <int D>
+__device__ __forceinline__ void coarse_affinities(
+    const DevPlan& pl, const void* kbar, const void* q, float scale_log2,
+    const BlockDesc& qb, int h, int kvh, int first, int nh, int r0, int wave,
+    float* ev, int stride, int lane) {
+  constexpr int KS = D / 32;
+  const int i16 = lane & 15, kg = lane >> 4;
+  const int ntile = (nh + 15) / 16;
+  const size_t lo_off = (size_t)pl.hkv * pl.nb * D;
+  const __bf16* const k0 =
+      (const __bf16*)kbar + (((size_t)kvh * (D / 8) + kg) * pl.nb + first) * 8;
+  const size_t step = (size_t)4 * pl.nb * 8;
+  bf16x8 kh[KS], kl[KS];
+  auto load = [&](int t) {
+    const __bf16* const p = k0 + (size_t)min(16 * t + i16, nh - 1) * 8;
+#pragma unroll
+    for (int u = 0; u < KS; ++u) {
+      kh[u] = *(const bf16x8*)(p + u * step);
+      kl[u] = *(const bf16x8*)(p + lo_off + u * step);
+    }
+  };
+  if (wave < ntile) load(wave);
+  const __bf16* const qr =
+      (const __bf16*)q +
+      ((size_t)(qb.start + min(r0 + i16, qb.len - 1)) * pl.hq + h) * D + 8 * kg;
+  bf16x8 qf[KS];
+#pragma unroll
+  for (int u = 0; u < KS; ++u) qf[u] = *(const bf16x8*)(qr + 32 * u);
+  for (int t = wave; t < ntile; t += kCoarseAff) {
+    bf16x8 ch[KS], cl[KS];
+#pragma unroll
+    for (int u = 0; u < KS; ++u) {
+      ch[u] = kh[u];
+      cl[u] = kl[u];
+    }
+    if (t + kCoarseAff < ntile) load(t + kCoarseAff);
+    f32x4 acc = {};
+#pragma unroll
+    for (int u = 0; u < KS; ++u) {
+      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ch[u], qf[u], acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(cl[u], qf[u], acc, 0, 0, 0);
+    }
+    const int j = 16 * t + 4 * kg;
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      acc[e] = j + e < nh ? acc[e] * scale_log2 : neg_inf();
+    *(f32x4*)(ev + i16 * stride + j) = acc;
+  }
+}
+
 template <bool F32, int D>
 __global__ __launch_bounds__(kCoarseThreads) void coarse_kernel(
     const DevPlan pl, const Workspace ws, const SelCall sc,
     float* __restrict__ cpart) {
-  constexpr int TPR = kCoarseTPR, RPW = kCoarseRows;
-  constexpr int NW = (kRegVals + 31) / 32;
+  constexpr int RPW = kCoarseRows;
   extern __shared__ __attribute__((aligned(16))) float dyn[];
   const int tile = blockIdx.x, h = blockIdx.y, pass = blockIdx.z;
   const TextTile tt = pl.tiles[tile];
@@ -887,36 +945,102 @@ __global__ __launch_bounds__(kCoarseThreads) void coarse_kernel(
     for (int j = tid; j < Wb; j += kCoarseThreads) dst[j] = 0.f;
     return;
   }
-  const int L = sel_per_thread(nh, TPR), stride = sel_stride(nh, TPR);
+  const int stride = coarse_stride(nh);
   float* const ev = dyn;                      // [RPW][stride]
-  float* const emx = dyn + RPW * stride;      // [waves][32 rows]
-  float* const esm = emx + kCoarseWaves * 32;
+  float* const emx = dyn + RPW * stride;      // [exact waves][32 rows]
+  float* const esm = emx + kCoarseExact * 32;
   const int kvh = h / (pl.hq / pl.hkv);
   const int first = qbid - nh;                // first visual block
   const SeqDesc sq = pl.seqs[tt.seq];
   const int nsys = (sq.vis0 - sq.tok0 + kTile64 - 1) / kTile64;
-  affinity_tiles<F32, D>(pl, ws.kbar, sc.q, sc.scale_log2, qb, h, kvh, first,
-                         nh, TPR * L, r0, RPW, 0, wave, kCoarseWaves, ev,
-                         stride, lane);
-  // the E_i tiles from the last wave down (the first ones have one affinity
-  // tile more)
-  float mw, lw;
-  exact_part<F32, D>(pl, sc, qb, qbid, h, kvh, first - nsys, nsys, r0,
-                     kCoarseWaves - 1 - wave, lane, mw, lw);
-  if ((lane >> 5) == 0) {
-    emx[wave * 32 + lane] = mw;
-    esm[wave * 32 + lane] = lw;
+  if (wave < kCoarseAff) {
+    if (F32)
+      affinity_tiles<F32, D>(pl, ws.kbar, sc.q, sc.scale_log2, qb, h, kvh,
+                             first, nh, nh, r0, RPW, 0, wave, kCoarseAff,
+                             ev, stride, lane, nullptr);
+    else
+      coarse_affinities<D>(pl, ws.kbar, sc.q, sc.scale_log2, qb, h, kvh, first,
+                           nh, r0, wave, ev, stride, lane);
+  } else {
+    const int e0 = wave - kCoarseAff;
+    float mw, lw;
+    exact_part<F32, D>(pl, sc, qb, h, kvh, first - nsys, nsys, r0, e0, lane, mw,
+                       lw);
+    if ((lane >> 5) == 0) {
+      emx[e0 * 32 + lane] = mw;
+      esm[e0 * 32 + lane] = lw;
+    }
   }
   __syncthreads();
   const int row = r0 + wave;                  // one row per wave
   if (row < qb.len) {
-    float* const my = ev + wave * stride + lane * L;
-    float v[kRegVals], mx;
-    unsigned kept[NW];
-    retain_regs<TPR, kRegVals, NW>(my, L, nh, sc.tau, lane, lane, v, kept, mx);
-    // E_i: the waves' parts, in tile order
+    // The row's history, block 64 i + lane in v[i]: e_j = exp2(g_j - max),
+    // and the cut t* by the bisection of retain_row_regs. Every bound is
+    // uniform over the wave, and the entries at or above a pivot are counted
+    // from the compare masks by the scalar unit, so a pass is three vector
+    // instructions per entry and the sum over the lanes.
+    float* const my = ev + wave * stride;
+    const int ni = (nh + 63) >> 6;
+    float v[kCoarseVals];
+    float mx = neg_inf();
+    auto each = [&](auto fn) {   // fn(i) for i < ni, a group of four at a time
+#pragma unroll
+      for (int c = 0; c < kCoarseVals / 4; ++c)
+        if (4 * c < ni) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) fn(4 * c + e);
+        }
+    };
+    each([&](int i) {
+      const int j = 64 * i + lane;
+      v[i] = j < nh ? my[j] : neg_inf();
+      mx = fmaxf(mx, v[i]);
+    });
+    mx = grp_max<64>(mx);
+    float z = 0.f;
+    unsigned kmin = 0xFFFFFFFFu;
+    each([&](int i) {
+      v[i] = __builtin_amdgcn_exp2f(v[i] - mx);
+      z += v[i];
+      kmin = min(kmin, __float_as_uint(v[i]) - 1u);   // +0 wraps to the top
+    });
+    const float thr = sc.tau * grp_sum<64>(z);
+    unsigned lo = __builtin_amdgcn_readfirstlane(grp_minu<64>(kmin) + 1u);
+    unsigned hi = __float_as_uint(1.f) + 1u;   // the largest e is exactly 1
+    int clo = nh, chi = 0;
+    float fhi = 0.f;
+    while (hi - lo > 1u && clo - chi > 1) {
+      const unsigned mid = lo + ((hi - lo) >> 1);
+      float f = 0.f;
+      int k = 0;
+      each([&](int i) {
+        const bool in = __float_as_uint(v[i]) >= mid;
+        f += in ? v[i] : 0.f;
+        k += __popcll(__ballot(in));
+      });
+      const float F = __uint_as_float(__builtin_amdgcn_readfirstlane(
+          __float_as_uint(grp_sum<64>(f))));
+      if (F >= thr) {
+        lo = mid;
+        clo = k;
+      } else {
+        hi = mid;
+        chi = k;
+        fhi = F;
+      }
+    }
+    // equal values at the cut: taken in block order until thr is reached
+    int take = clo - chi;
+    if (take > 1) {
+      float cum = fhi;
+      int t = 0;
+      for (; t < take && cum < thr; ++t) cum += __uint_as_float(lo);
+      take = t;
+    }
+    int before = 0;   // entries at the cut in lower blocks
+    // E_i: the two waves' parts
     float mE = -__builtin_inff(), lE = 0.f;
-    for (int w = kCoarseWaves - 1; w >= 0; --w) {
+    for (int w = 0; w < kCoarseExact; ++w) {
       const float m = emx[w * 32 + wave], l = esm[w * 32 + wave];
       if (m == -__builtin_inff()) continue;
       const float mn = fmaxf(mE, m);
@@ -926,26 +1050,32 @@ __global__ __launch_bounds__(kCoarseThreads) void coarse_kernel(
       mE = mn;
     }
     // a history block holds 64 tokens, except the video's last visual one
-    const int jl = (sq.txt0 - sq.vis0 + kTile64 - 1) / kTile64 - 1 - lane * L;
-    const float last = (float)pl.blocks[first + jl + lane * L].len;
+    const int nvis = sq.txt0 - sq.vis0, nvb = (nvis + kTile64 - 1) / kTile64;
+    const float last = (float)(nvis - (nvb - 1) * kTile64);
     const float M = fmaxf(mx + 6.f, mE);      // 6 = log2(64)
     const float up = __builtin_amdgcn_exp2f(mx - M);
-    float z = 0.f;
-#pragma unroll
-    for (int i = 0; i < kRegVals; ++i) {
-      const float len = i == jl ? last : (float)kTile64;
-      v[i] = (kept[i >> 5] >> (i & 31)) & 1u ? v[i] * up * len : 0.f;
-      z += v[i];
-    }
-    z = grp_sum<TPR>(z) + lE * __builtin_amdgcn_exp2f(mE - M);
-    const float inv = 1.f / z;
-#pragma unroll
-    for (int c = 0; c < kRegVals / 4; ++c)
-      if (4 * c < L) {
-        const f32x4 t = {v[4 * c] * inv, v[4 * c + 1] * inv,
-                         v[4 * c + 2] * inv, v[4 * c + 3] * inv};
-        *(f32x4*)(my + 4 * c) = t;
+    z = 0.f;
+    each([&](int i) {
+      const unsigned kb = __float_as_uint(v[i]);
+      bool kept = kb >= lo;
+      if (clo - chi > take) {
+        const unsigned long long tie = __ballot(kb == lo);
+        const int rank = before + __builtin_amdgcn_mbcnt_hi(
+            (unsigned)(tie >> 32),
+            __builtin_amdgcn_mbcnt_lo((unsigned)tie, 0u));
+        kept = kept && (kb != lo || rank < take);
+        before += __popcll(tie);
       }
+      const float len = 64 * i + lane == nvb - 1 ? last : (float)kTile64;
+      v[i] = kept ? v[i] * up * len : 0.f;
+      z += v[i];
+    });
+    z = grp_sum<64>(z) + lE * __builtin_amdgcn_exp2f(mE - M);
+    const float inv = 1.f / z;
+    each([&](int i) {
+      const int j = 64 * i + lane;
+      if (j < nh) my[j] = v[i] * inv;
+    });
   }
   __syncthreads();
   for (int j = tid; j < Wb; j += kCoarseThreads) {
@@ -967,13 +1097,12 @@ __global__ __launch_bounds__(256) void coarse_reduce_kernel(
   const int Wb = pl.W * 32;
   float t = 0.f;
   if (sq.n_tiles > 0) {
-    const int qb0 = pl.tiles[sq.tile0].qblock;
-    const int first = qb0 - pl.blk_local[qb0];
     const int j = (int)(((int64_t)(f - sq.frame0) * pl.Nv) / kTile64);
     for (int ti = sq.tile0; ti < sq.tile0 + sq.n_tiles; ++ti)
       for (int ps = 0; ps < kCoarsePasses; ++ps)
         t += cpart[(((size_t)ti * kCoarsePasses + ps) * pl.hq + h) * Wb + j];
-    t *= (float)pl.Nv / (float)pl.blocks[first + j].len;
+    t *= (float)pl.Nv /
+         (float)min(kTile64, sq.txt0 - sq.vis0 - j * kTile64);
   }
   out[(size_t)h * pl.T + f] = t;
 }
@@ -1081,8 +1210,8 @@ hipError_t launch_coarse(const DevPlan& p, const Workspace& w,
   if (p.n_tiles > 0) {
     const int nh_max = std::max(p.hmax, 1);
     const size_t lds =
-        (size_t)kCoarseRows * sel_stride(nh_max, kCoarseTPR) * 4 +
-        2 * kCoarseWaves * 32 * 4;
+        (size_t)kCoarseRows * coarse_stride(nh_max) * 4 +
+        2 * kCoarseExact * 32 * 4;
     dim3 grid(p.n_tiles, p.hq, kCoarsePasses), block(kCoarseThreads);
     auto go = [&](auto fn) -> hipError_t {
       if (lds > 64 * 1024) {

@@ -79,10 +79,10 @@ def _layout(w):
     return Layout(ns, nf, nt, w.tokens_per_frame)
 
 
-def _gpu_coarse(w, mask, l=0):
+def _gpu_coarse(w, mask, l=0, inputs=None):
     import torch
     ev = pytest.ev
-    q, k, _ = to_device(wl.gen_layer(w, l), w, torch)
+    q, k, _ = to_device(inputs or wl.gen_layer(w, l), w, torch)
     T = mask.stats["n_frames_total"]
     out = torch.full((w.hq, T), float("nan"), device="cuda")
     ws = torch.empty(ev.sparse_prefill_workspace(mask, w.d),
@@ -97,12 +97,19 @@ def test_coarse_evidence_history_edges(name):
     _check_coarse(name, EDGES[name])
 
 
+@pytest.mark.parametrize("name", ["share_4", "share_8_short", "fp32_share_8"])
+def test_coarse_evidence_ties(name):
+    """All affinities equal (Q = 0): the lowest blocks are kept."""
+    w = EDGES[name]
+    _check_coarse(name, w, wl.gen_layer(w, 0, q_override="zero"))
+
+
 @pytest.mark.parametrize("name", list(CASES))
 def test_coarse_evidence(name):
     _check_coarse(name, CASES[name])
 
 
-def _check_coarse(name, w):
+def _check_coarse(name, w, inputs=None):
     ev = pytest.ev
     say(f"case {name}")
     lay = _layout(w)
@@ -111,13 +118,14 @@ def _check_coarse(name, w):
     mask = ev.build_block_mask(nf, nt, w.tokens_per_frame, w.block,
                                w.sink_blocks, w.window, w.hq, w.hkv,
                                n_sys=ns, tau_p=w.tau_p)
-    Eg = _gpu_coarse(w, mask)
-    q, k, _ = wl.gen_layer(w, 0).as_f64()
+    inputs = inputs or wl.gen_layer(w, 0)
+    Eg = _gpu_coarse(w, mask, inputs=inputs)
+    q, k, _ = inputs.as_f64()
     txt = lay.text_rows()
     keep, info = topp.select(q, k, lay, blk, w.tau_p, w.softmax_scale, txt)
     Eo = coarse.query_frame(lay, coarse.coarse_probs(
         q, k, lay, blk, keep, txt, w.softmax_scale), w.hq)
-    rb, _ = _gpu_bits(ev, mask, w, 0)
+    rb, _ = _gpu_bits(ev, mask, w, 0, inputs=inputs)
     kg = _keep_of_rows(ev, rb, mask, blk, txt, keep.shape[2])
     okf = np.ones_like(Eo, bool)
     for h, j in zip(*np.nonzero((kg != keep).any(axis=2))):
