@@ -568,16 +568,17 @@ evisel_status evisel_sparse_prefill(const evisel_mask* m, int32_t layer,
       s);
   if (e != hipSuccess) return hip_fail(e, "combine and evidence launch");
   if (prof) prof_record(call, 3, s);
-  if (frame_pairs) {
-    e = evisel::launch_frame_pairs(
-        m->dp, w, frame_pairs + (size_t)layer * P.pairs.size(), s);
-    if (e != hipSuccess) return hip_fail(e, "frame pair launch");
-  }
   if (intra_frame) {
-    const size_t nv = (size_t)P.layout.Nv;
-    e = evisel::launch_intra_frame(
-        m->dp, w, c, intra_frame + (size_t)layer * P.T * nv * nv, s);
+    e = evisel::launch_intra_frame(m->dp, w, c, s);
     if (e != hipSuccess) return hip_fail(e, "intra-frame launch");
+  }
+  if (cues) {
+    const size_t maps = (size_t)P.T * P.layout.Nv * P.layout.Nv;
+    e = evisel::launch_cue_finish(
+        m->dp, w,
+        frame_pairs ? frame_pairs + (size_t)layer * P.pairs.size() : nullptr,
+        intra_frame ? intra_frame + (size_t)layer * maps : nullptr, s);
+    if (e != hipSuccess) return hip_fail(e, "frame cue launch");
   }
   if (prof) {
     prof_record(call, 4, s);

@@ -66,7 +66,6 @@
 // each chunk leaves an unnormalised partial (acc, m_ref, row sum, non-visual
 // mass) in the workspace, and the combine part of combine_evidence_kernel
 // merges them.
-#include <algorithm>
 #include <type_traits>
 
 #include "attn_f32.h"
@@ -530,8 +529,8 @@ attn_kernel(const DevPlan pl, const Workspace ws, const AttnCall ac) {
 // LDS once; waves 0-1 take the even heads of each head pair, waves 2-3 the
 // odd ones, the next pair's Q and LSE are fetched while the current pair is
 // computed, and the two wave groups' sums are added in a fixed order. The
-// result is a partial per kv head; intra_reduce_kernel adds the kv heads in
-// order and divides by Hq.
+// result is a partial per kv head; cue_finish_kernel adds the kv heads in order
+// and divides by Hq.
 template <class P, int D>
 __global__ __attribute__((amdgpu_flat_work_group_size(kThreads, kThreads)))
 void intra_kernel(const DevPlan pl, const Workspace ws, const AttnCall ac) {
@@ -653,18 +652,6 @@ void intra_kernel(const DevPlan pl, const Workspace ws, const AttnCall ac) {
     }
 }
 
-__global__ __launch_bounds__(256) void intra_reduce_kernel(
-    const DevPlan pl, const Workspace ws, float* __restrict__ out) {
-  const size_t n = (size_t)pl.T * pl.Nv * pl.Nv;
-  const float inv = 1.f / (float)pl.hq;
-  for (size_t e = (size_t)blockIdx.x * 256 + threadIdx.x; e < n;
-       e += (size_t)gridDim.x * 256) {
-    float t = 0.f;
-    for (int kvh = 0; kvh < pl.hkv; ++kvh) t += ws.intra_part[kvh * n + e];
-    out[e] = t * inv;
-  }
-}
-
 }  // namespace
 
 hipError_t launch_attention(const DevPlan& p, const Workspace& w,
@@ -702,7 +689,7 @@ hipError_t launch_attention(const DevPlan& p, const Workspace& w,
 }
 
 hipError_t launch_intra_frame(const DevPlan& p, const Workspace& w,
-                              const AttnCall& c, float* out, hipStream_t s) {
+                              const AttnCall& c, hipStream_t s) {
   dim3 grid(p.nb, p.hkv), block(kThreads);
   if (c.fp32) {
     if (c.d == 64)
@@ -715,11 +702,6 @@ hipError_t launch_intra_frame(const DevPlan& p, const Workspace& w,
     else
       intra_kernel<Bf16Path<128>, 128><<<grid, block, 0, s>>>(p, w, c);
   }
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  const size_t n = (size_t)p.T * p.Nv * p.Nv;
-  const int blocks = (int)std::min<size_t>((n + 255) / 256, 4096);
-  intra_reduce_kernel<<<dim3(blocks), dim3(256), 0, s>>>(p, w, out);
   return hipGetLastError();
 }
 

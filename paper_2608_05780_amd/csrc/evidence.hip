@@ -303,23 +303,19 @@ __device__ __forceinline__ void e_ff_part(const DevPlan& pl,
   }
 }
 
-__global__ __launch_bounds__(kFmThreads) void frame_mean_kernel(
-    const DevPlan pl, const float* __restrict__ ev, int n_layers,
-    float* __restrict__ e_layer, float* __restrict__ e_qf,
-    const float* __restrict__ pairs, float* __restrict__ e_ff) {
-  __shared__ float red[kFmLayers][kFmFrames];
-  const int n_mean = (pl.T + kFmFrames - 1) / kFmFrames;
-  if ((int)blockIdx.x >= n_mean) {
-    e_ff_part(pl, pairs, n_layers,
-              ((int)blockIdx.x - n_mean) * (kFmThreads / 64) +
-                  (int)(threadIdx.x >> 6),
-              e_ff);
-    return;
-  }
+// Means of frames t0 .. t0 + 31 (t < t_end stored): the caller's 1,024
+// threads are 32 frames x 32 layer groups, layers added in a fixed order. The
+// first 32 threads return the frames' pooled means.
+__device__ __forceinline__ float mean_part(const DevPlan& pl,
+                                           const float* __restrict__ ev,
+                                           int n_layers, int t0, int t_end,
+                                           float (&red)[kFmLayers][kFmFrames],
+                                           float* __restrict__ e_layer,
+                                           float* __restrict__ e_qf) {
   const int tl = threadIdx.x % kFmFrames, lg = threadIdx.x / kFmFrames;
-  const int t = blockIdx.x * kFmFrames + tl;
+  const int t = t0 + tl;
   float part = 0.f;
-  if (t < pl.T) {
+  if (t < t_end) {
     const SeqDesc sq = pl.seqs[pl.frame_seq[t]];
     const float denom = (float)pl.hq * (float)sq.n_text;
     for (int l = lg; l < n_layers; l += kFmLayers) {
@@ -335,16 +331,78 @@ __global__ __launch_bounds__(kFmThreads) void frame_mean_kernel(
   }
   red[lg][tl] = part;
   __syncthreads();
-  if (lg == 0 && t < pl.T) {
-    float pooled = 0.f;
+  float pooled = 0.f;
+  if (lg == 0 && t < t_end) {
 #pragma unroll
     for (int i = 0; i < kFmLayers; ++i) pooled += red[i][tl];
-    e_qf[t] = pooled / (float)n_layers;
+    pooled /= (float)n_layers;
+    e_qf[t] = pooled;
   }
+  return pooled;
 }
 
 __device__ __forceinline__ float rank_key(float x) {
   return x != x ? -__builtin_inff() : x;   // NaN ranks like -inf
+}
+
+// Output offset of video n's top-k: the earlier videos' counts (one wave).
+__device__ __forceinline__ int topk_offset(const DevPlan& pl,
+                                           const int* __restrict__ kps, int n,
+                                           int lane) {
+  int off = 0;
+  for (int i = lane; i < n; i += 64)
+    off += min(max(kps[i], 0), pl.seqs[i].n_frames);
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) off += __shfl_xor(off, o);
+  return off;
+}
+
+// SMALL (no video has more than kTopkFrames frames): one work-group per video
+// takes its means in two steps of 32 frames and ranks them itself, so that a
+// short probe needs one launch here and not two (32 fp32 frames to their
+// top-k: 44.6 us with two, 43.2 with one).
+constexpr int kTopkFrames = 64;
+
+template <bool SMALL>
+__global__ __launch_bounds__(kFmThreads) void frame_mean_kernel(
+    const DevPlan pl, const float* __restrict__ ev, int n_layers,
+    float* __restrict__ e_layer, float* __restrict__ e_qf,
+    const int* __restrict__ kps, int* __restrict__ topk,
+    const float* __restrict__ pairs, float* __restrict__ e_ff) {
+  __shared__ float red[kFmLayers][kFmFrames];
+  const int n_mean = SMALL ? pl.n_seq : (pl.T + kFmFrames - 1) / kFmFrames;
+  if ((int)blockIdx.x >= n_mean) {
+    e_ff_part(pl, pairs, n_layers,
+              ((int)blockIdx.x - n_mean) * (kFmThreads / 64) +
+                  (int)(threadIdx.x >> 6),
+              e_ff);
+    return;
+  }
+  if constexpr (!SMALL) {
+    mean_part(pl, ev, n_layers, blockIdx.x * kFmFrames, pl.T, red, e_layer,
+              e_qf);
+  } else {
+    __shared__ float score[kTopkFrames];
+    const int n = blockIdx.x, lane = threadIdx.x & 63;
+    const SeqDesc sq = pl.seqs[n];
+    const int F = sq.n_frames;
+    for (int f0 = 0; f0 < F; f0 += kFmFrames) {
+      if (f0) __syncthreads();   // red is free
+      const float e = mean_part(pl, ev, n_layers, sq.frame0 + f0,
+                                sq.frame0 + F, red, e_layer, e_qf);
+      if (threadIdx.x < kFmFrames)
+        score[f0 + threadIdx.x] = rank_key(e);
+    }
+    __syncthreads();
+    if (threadIdx.x >= 64) return;
+    const int k = min(max(kps[n], 0), F);
+    const int off = topk_offset(pl, kps, n, lane);
+    const float v = score[min(lane, F - 1)];
+    int rank = 0;
+    for (int u = 0; u < F; ++u)
+      rank += score[u] > v || (score[u] == v && u < lane);
+    if (lane < F && rank < k) topk[off + rank] = lane;
+  }
 }
 
 // One work-group per video and 64 of its frames (lane = frame): the video's
@@ -354,7 +412,6 @@ __device__ __forceinline__ float rank_key(float x) {
 // and the wavefronts' counts are added. A frame costs two instructions per
 // score and wavefront; one work-group per video (each frame against all
 // scores, one LDS read each) took 60 us on 1,024 frames.
-constexpr int kTopkFrames = 64;
 constexpr int kTopkThreads = 512;
 constexpr int kTopkWaves = kTopkThreads / 64;
 constexpr int kTopkChunk = 4096;
@@ -414,12 +471,7 @@ __global__ __launch_bounds__(kTopkThreads) void topk_kernel(
   rank = 0;
 #pragma unroll
   for (int w = 0; w < kTopkWaves; ++w) rank += part[w][lane];
-  // output offset: the earlier videos' counts
-  int off = 0;
-  for (int i = lane; i < n; i += 64)
-    off += min(max(kps[i], 0), pl.seqs[i].n_frames);
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) off += __shfl_xor(off, o);
+  const int off = topk_offset(pl, kps, n, lane);
   if (t < F && rank < k) topk[off + rank] = t;
 }
 
@@ -434,10 +486,10 @@ constexpr int kPairWaves = 4;
 
 constexpr int kPairHeads = 8;
 
-__global__ __launch_bounds__(64 * kPairWaves) void frame_pairs_kernel(
-    const DevPlan pl, const Workspace ws, float* __restrict__ out) {
+__device__ __forceinline__ void frame_pair(const DevPlan& pl,
+                                           const Workspace& ws, int pi,
+                                           float* __restrict__ out) {
   const int lane = threadIdx.x & 63;
-  const int pi = blockIdx.x * kPairWaves + (threadIdx.x >> 6);
   if (pi >= pl.n_pairs) return;
   const FramePair fp = pl.pairs[pi];
   const int fpt = 64 / pl.Nv;
@@ -483,13 +535,52 @@ __global__ __launch_bounds__(64 * kPairWaves) void frame_pairs_kernel(
   if (lane == 0) out[pi] = acc / ((float)pl.hq * (float)pl.Nv);
 }
 
+// The frame cues' last step, one launch (256 frames x 64 tokens, 28/4 heads: the
+// layer takes 254.7 us, 262.1 with two launches): work-groups [0, n_pair_blocks) take
+// the cross-frame pairs, the others the intra-frame maps, whose partial sums
+// per kv head (intra_kernel) are added in kv head order and divided by Hq.
+constexpr int kReduceVec = 4;   // map entries per thread (N_v^2 is a multiple)
+
+__global__ __launch_bounds__(64 * kPairWaves) void cue_finish_kernel(
+    const DevPlan pl, const Workspace ws, int n_pair_blocks,
+    float* __restrict__ pairs_out, float* __restrict__ intra_out) {
+  if ((int)blockIdx.x < n_pair_blocks) {
+    frame_pair(pl, ws, blockIdx.x * kPairWaves + (int)(threadIdx.x >> 6),
+               pairs_out);
+    return;
+  }
+  const size_t n = (size_t)pl.T * pl.Nv * pl.Nv;
+  const size_t e = ((size_t)(blockIdx.x - n_pair_blocks) * (64 * kPairWaves) +
+                    threadIdx.x) * kReduceVec;
+  if (e >= n) return;
+  const float inv = 1.f / (float)pl.hq;
+  f32x4 t = {};
+  for (int kvh = 0; kvh < pl.hkv; ++kvh)
+    t += *(const f32x4*)(ws.intra_part + kvh * n + e);
+  t *= inv;
+  float* const dst = intra_out + e;
+  if (((uintptr_t)dst & 15) == 0) {
+    *(f32x4*)dst = t;
+  } else {   // the caller's map is 4-byte aligned only
+#pragma unroll
+    for (int i = 0; i < kReduceVec; ++i) dst[i] = t[i];
+  }
+}
+
 }  // namespace
 
-hipError_t launch_frame_pairs(const DevPlan& p, const Workspace& w,
-                              float* pairs_out, hipStream_t s) {
-  if (p.n_pairs == 0) return hipSuccess;
-  frame_pairs_kernel<<<dim3((p.n_pairs + kPairWaves - 1) / kPairWaves),
-                       dim3(64 * kPairWaves), 0, s>>>(p, w, pairs_out);
+hipError_t launch_cue_finish(const DevPlan& p, const Workspace& w,
+                             float* pairs_out, float* intra_out,
+                             hipStream_t s) {
+  const int pb =
+      pairs_out ? (p.n_pairs + kPairWaves - 1) / kPairWaves : 0;
+  const size_t n = intra_out ? (size_t)p.T * p.Nv * p.Nv : 0;
+  constexpr size_t kPer = 64 * kPairWaves * kReduceVec;
+  const size_t blocks = pb + (n + kPer - 1) / kPer;
+  if (blocks == 0) return hipSuccess;
+  if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
+  cue_finish_kernel<<<dim3((unsigned)blocks), dim3(64 * kPairWaves), 0, s>>>(
+      p, w, pb, pairs_out, intra_out);
   return hipGetLastError();
 }
 
@@ -522,7 +613,8 @@ hipError_t launch_frame_evidence(const DevPlan& p, const float* evidence,
                                  float* e_qf, const int32_t* k_per_seq,
                                  int32_t* topk, const float* pairs,
                                  float* e_ff, hipStream_t s) {
-  int64_t blocks = (p.T + kFmFrames - 1) / kFmFrames;
+  const bool small = k_per_seq && p.max_frames <= kTopkFrames;
+  int64_t blocks = small ? p.n_seq : (p.T + kFmFrames - 1) / kFmFrames;
   if (e_ff) {
     constexpr int kWaves = kFmThreads / 64;
     const int64_t waves =
@@ -530,10 +622,15 @@ hipError_t launch_frame_evidence(const DevPlan& p, const float* evidence,
     blocks += (waves + kWaves - 1) / kWaves;
   }
   if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
-  frame_mean_kernel<<<dim3((unsigned)blocks), dim3(kFmThreads), 0, s>>>(
-      p, evidence, n_layers, e_qf_layer, e_qf, pairs, e_ff);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess || !k_per_seq) return e;
+  const dim3 grid((unsigned)blocks), block(kFmThreads);
+  if (small)
+    frame_mean_kernel<true><<<grid, block, 0, s>>>(
+        p, evidence, n_layers, e_qf_layer, e_qf, k_per_seq, topk, pairs, e_ff);
+  else
+    frame_mean_kernel<false><<<grid, block, 0, s>>>(
+        p, evidence, n_layers, e_qf_layer, e_qf, k_per_seq, topk, pairs, e_ff);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess || !k_per_seq || small) return e;
   // (at most 65,536 frames per video: 1,024 in y)
   topk_kernel<<<dim3(p.n_seq, (p.max_frames + kTopkFrames - 1) / kTopkFrames),
                 dim3(kTopkThreads), 0, s>>>(p, e_qf, k_per_seq, topk);

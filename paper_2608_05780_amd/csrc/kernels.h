@@ -119,11 +119,13 @@ hipError_t launch_frame_evidence(const DevPlan& p, const float* evidence,
                                  float* e_qf, const int32_t* k_per_seq,
                                  int32_t* topk, const float* pairs,
                                  float* e_ff, hipStream_t s);
-// Cross-frame cue of one layer: pairs_out[i] = A_ff of pair i.
-hipError_t launch_frame_pairs(const DevPlan& p, const Workspace& w,
-                              float* pairs_out, hipStream_t s);
-// Intra-frame cue of one layer: out [T][N_v][N_v].
+// Intra-frame cue of one layer: partial maps per kv head (workspace).
 hipError_t launch_intra_frame(const DevPlan& p, const Workspace& w,
-                              const AttnCall& c, float* out, hipStream_t s);
+                              const AttnCall& c, hipStream_t s);
+// The frame cues of one layer: pairs_out[i] = A_ff of pair i, intra_out
+// [T][N_v][N_v] from the partial maps (either may be null).
+hipError_t launch_cue_finish(const DevPlan& p, const Workspace& w,
+                             float* pairs_out, float* intra_out,
+                             hipStream_t s);
 
 }  // namespace evisel

@@ -21,6 +21,8 @@ CASES = {   # frames per video, k per video, layers, heads
     "groups": ((63, 64, 65, 1, 130), (5, 64, 0, 9, 130), 8, 4),
     "chunks": ((4095, 4097, 4161), (300, -3, 5000), 1, 1),
     "layers_15": ((40,), (7,), 15, 28),
+    # no video past 64 frames: means and ranks in one work-group per video
+    "short_videos": ((64, 33, 1, 32, 31), (5, 40, 1, 0, 31), 35, 4),
 }
 
 
