@@ -753,11 +753,10 @@ __global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(
 // lane's registers). The grid is small (a few hundred work-groups whatever
 // the history), so latency bounds it: 16 waves share a work-group's
 // affinity tiles and every row is searched at once, its bounds in scalar
-// registers. The whole call (means, this kernel, the reduction) takes 25.5 us
-// on 256 frames x 64 tokens + 128 query tokens and 44.1 us on 1,024 frames
+// registers. The whole call (means, this kernel, the reduction) takes 26.5 us
+// on 256 frames x 64 tokens + 128 query tokens and 46.7 us on 1,024 frames
 // (28/4 heads, d = 128, bf16), against 183 us and 3.6 ms when the retention
-// of every row was decided first (30.4 and 46.7 us with the lane-group search
-// of select_kernel on 64 lanes). The per-block masses of the pass's rows are summed in row order
+// of every row was decided first. The per-block masses of the pass's rows are summed in row order
 // into cpart; coarse_reduce_kernel adds a video's blocks and passes in order
 // and spreads each block's mass evenly over its frames (frames never cross
 // blocks).
@@ -975,10 +974,14 @@ __global__ __launch_bounds__(kCoarseThreads) void coarse_kernel(
   const int row = r0 + wave;                  // one row per wave
   if (row < qb.len) {
     // The row's history, block 64 i + lane in v[i]: e_j = exp2(g_j - max),
-    // and the cut t* by the bisection of retain_row_regs. Every bound is
-    // uniform over the wave, and the entries at or above a pivot are counted
-    // from the compare masks by the scalar unit, so a pass is three vector
-    // instructions per entry and the sum over the lanes.
+    // and the cut t* by a bisection over the bit patterns as in
+    // retain_row_regs, on the mass that is dropped: t* is the largest value
+    // below which at most (1 - tau) Z lies. That mass is a few per cent of Z,
+    // so its fp32 sum rounds correspondingly less than the kept mass would
+    // and fewer cuts fall within rounding (on the kept mass 25.5 and 44.0 us). Every bound is uniform over the
+    // wave, and the entries at or above a pivot are counted from the compare
+    // masks by the scalar unit, so a pass is three vector instructions per
+    // entry and the sum over the lanes.
     float* const my = ev + wave * stride;
     const int ni = (nh + 63) >> 6;
     float v[kCoarseVals];
@@ -1004,39 +1007,38 @@ __global__ __launch_bounds__(kCoarseThreads) void coarse_kernel(
       z += v[i];
       kmin = min(kmin, __float_as_uint(v[i]) - 1u);   // +0 wraps to the top
     });
-    const float thr = sc.tau * grp_sum<64>(z);
+    const float drop = (float)(1.0 - (double)sc.tau) * grp_sum<64>(z);
     unsigned lo = __builtin_amdgcn_readfirstlane(grp_minu<64>(kmin) + 1u);
     unsigned hi = __float_as_uint(1.f) + 1u;   // the largest e is exactly 1
     int clo = nh, chi = 0;
-    float fhi = 0.f;
+    float glo = 0.f;   // mass below lo
     while (hi - lo > 1u && clo - chi > 1) {
       const unsigned mid = lo + ((hi - lo) >> 1);
       float f = 0.f;
       int k = 0;
       each([&](int i) {
         const bool in = __float_as_uint(v[i]) >= mid;
-        f += in ? v[i] : 0.f;
+        f += in ? 0.f : v[i];
         k += __popcll(__ballot(in));
       });
-      const float F = __uint_as_float(__builtin_amdgcn_readfirstlane(
+      const float G = __uint_as_float(__builtin_amdgcn_readfirstlane(
           __float_as_uint(grp_sum<64>(f))));
-      if (F >= thr) {
+      if (G <= drop) {
         lo = mid;
         clo = k;
+        glo = G;
       } else {
         hi = mid;
         chi = k;
-        fhi = F;
       }
     }
-    // equal values at the cut: taken in block order until thr is reached
+    // equal values at the cut: as many as may go are dropped, the highest
+    // blocks first (one at least is needed: all of them exceed the mass)
     int take = clo - chi;
-    if (take > 1) {
-      float cum = fhi;
-      int t = 0;
-      for (; t < take && cum < thr; ++t) cum += __uint_as_float(lo);
-      take = t;
-    }
+    if (take > 1)
+      for (float cum = glo + __uint_as_float(lo); take > 1 && cum <= drop;
+           cum += __uint_as_float(lo))
+        --take;
     int before = 0;   // entries at the cut in lower blocks
     // E_i: the two waves' parts
     float mE = -__builtin_inff(), lE = 0.f;
