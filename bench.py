@@ -76,9 +76,11 @@ def measured_traffic():
 
 def attention_kernel_name(w, args):
     """The attention kernel the library launches for this run: the
-    pipelined kernel for bf16 inputs under the static rule (its frame-cue
-    form with the cues, for frames of 32 or 64 keys), attn_kernel
-    otherwise."""
+    pipelined kernel for bf16 inputs, under the static rule (its frame-cue
+    form with the cues, for frames of 32 or 64 keys) or, without the cues,
+    under top-p retention; attn_kernel otherwise."""
+    if w.dtype == "bf16" and w.tau_p > 0 and not args.cues:
+        return f"attn_pipe_topp_kernel<{w.d}>"
     if w.dtype == "bf16" and w.tau_p == 0 and (not args.cues or
                                                w.tokens_per_frame >= 32):
         return f"attn_pipe_kernel<{w.d}, {'true' if args.cues else 'false'}>"
