@@ -1002,15 +1002,16 @@ __global__ __launch_bounds__(kCoarseThreads) void coarse_kernel(
     mx = grp_max<64>(mx);
     float z = 0.f;
     unsigned kmin = 0xFFFFFFFFu;
+    int clo = 0, chi = 0;   // entries at or above lo and hi: +0 is below both
     each([&](int i) {
       v[i] = __builtin_amdgcn_exp2f(v[i] - mx);
       z += v[i];
       kmin = min(kmin, __float_as_uint(v[i]) - 1u);   // +0 wraps to the top
+      clo += __popcll(__ballot(v[i] != 0.f));
     });
     const float drop = (float)(1.0 - (double)sc.tau) * grp_sum<64>(z);
     unsigned lo = __builtin_amdgcn_readfirstlane(grp_minu<64>(kmin) + 1u);
     unsigned hi = __float_as_uint(1.f) + 1u;   // the largest e is exactly 1
-    int clo = nh, chi = 0;
     float glo = 0.f;   // mass below lo
     while (hi - lo > 1u && clo - chi > 1) {
       const unsigned mid = lo + ((hi - lo) >> 1);

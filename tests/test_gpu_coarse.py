@@ -104,6 +104,54 @@ def test_coarse_evidence_ties(name):
     _check_coarse(name, w, wl.gen_layer(w, 0, q_override="zero"))
 
 
+# Equal affinities at the cut beside blocks so far below that exp2 of their
+# difference is +0: the zeros are no ties and take no part in the count.
+# (tau, blocks at 0, blocks at about -6.9, blocks at -200 nats); the dropped
+# mass (1 - tau) Z is no multiple of a tie's, so the cut is not at rounding.
+UNDERFLOW = [(0.97, 64, 0, 10), (0.97, 64, 0, 1), (0.97, 64, 0, 2),
+             (0.97, 90, 0, 300), (0.5, 101, 0, 100), (0.97, 1, 100, 40),
+             (0.97, 1, 100, 1), (0.9, 3, 2000, 40), (0.97, 1, 0, 70)]
+
+
+@pytest.mark.parametrize("case", UNDERFLOW)
+def test_coarse_evidence_ties_beside_underflow(case):
+    tau, n_top, n_mid, n_far = case
+    ev = pytest.ev
+    F = n_top + n_mid + n_far
+    w = _w("underflow", d=64, hq=2, hkv=1, tokens_per_frame=64, n_frames=(F,),
+           n_text=(21,), n_sys=(0,), tau_p=float(np.float32(tau)),
+           plant_args={"count": 1, "s_frame": (2.0, 3.0), "s_query": 2.0})
+    inputs = wl.gen_layer(w, 0)
+    # affinity 16 k[0] / sqrt(64), in values that bf16 holds exactly
+    level = np.repeat([0.0, -3.453125, -100.0], [n_top, n_mid, n_far])
+    level = np.random.default_rng(3).permutation(level)
+    bf = lambda a: (a.astype(np.float32).view(np.uint32) >> 16).astype(
+        inputs.q.dtype)
+    q, k = np.zeros(inputs.q.shape), np.zeros(inputs.k.shape)
+    q[..., 0] = 16.0
+    k[:64 * F, 0, 0] = np.repeat(level, 64)
+    inputs.q, inputs.k = bf(q), bf(k)
+    lay = _layout(w)
+    blk = topp.Blocks(lay, w.block)
+    mask = ev.build_block_mask([F], [21], 64, 64, 1, 8, 2, 1, tau_p=w.tau_p)
+    Eg = _gpu_coarse(w, mask, inputs=inputs)
+    q, k, _ = inputs.as_f64()
+    txt = lay.text_rows()
+    keep, _ = topp.select(q, k, lay, blk, w.tau_p, w.softmax_scale, txt)
+    rb, _ = _gpu_bits(ev, mask, w, 0, inputs=inputs)
+    kg = _keep_of_rows(ev, rb, mask, blk, txt, keep.shape[2])
+    Eo = coarse.query_frame(lay, coarse.coarse_probs(
+        q, k, lay, blk, keep, txt, w.softmax_scale), w.hq)
+    say(f"  kept {int(keep[0, 0].sum())} of {F}, by the selection "
+        f"{int(kg[0, 0].sum())}, by the coarse pass {int((Eg[0] > 0).sum())}")
+    # every row is the same: a frame has mass where its block is kept
+    assert (keep == keep[:1, :1]).all()
+    seen = level > -100.0                      # the others' mass is below 1e-80
+    assert ((Eg > 0) == (keep[:, 0, :F] & seen)).all()
+    assert (kg[:, :, :F][:, :, seen] == keep[:, :, :F][:, :, seen]).all()
+    assert np.abs(Eg - Eo).max() <= 1e-5 * Eo.max()
+
+
 @pytest.mark.parametrize("name", list(CASES))
 def test_coarse_evidence(name):
     _check_coarse(name, CASES[name])
