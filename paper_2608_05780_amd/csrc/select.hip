@@ -1000,11 +1000,13 @@ __global__ __launch_bounds__(kCoarseThreads) void coarse_kernel(
       mx = fmaxf(mx, v[i]);
     });
     mx = grp_max<64>(mx);
+    // (every affinity -inf: no mass on the history, not NaN)
+    const float ref = mx == neg_inf() ? 0.f : mx;
     float z = 0.f;
     unsigned kmin = 0xFFFFFFFFu;
     int clo = 0, chi = 0;   // entries at or above lo and hi: +0 is below both
     each([&](int i) {
-      v[i] = __builtin_amdgcn_exp2f(v[i] - mx);
+      v[i] = __builtin_amdgcn_exp2f(v[i] - ref);
       z += v[i];
       kmin = min(kmin, __float_as_uint(v[i]) - 1u);   // +0 wraps to the top
       clo += __popcll(__ballot(v[i] != 0.f));

@@ -152,6 +152,22 @@ def test_coarse_evidence_ties_beside_underflow(case):
     assert np.abs(Eg - Eo).max() <= 1e-5 * Eo.max()
 
 
+def test_coarse_evidence_all_affinities_minus_infinite():
+    """Query rows whose every block affinity overflows to -inf put no mass on
+    the history."""
+    w = _w("minus-inf", d=64, hq=2, hkv=1, tokens_per_frame=32, n_frames=(9,),
+           n_text=(21,), n_sys=(0,))
+    inputs = wl.gen_layer(w, 0)
+    bf = lambda x: np.float32(x).view(np.uint32) >> 16
+    n = 9 * 32
+    inputs.k[:, :, 0] = 0
+    inputs.k[:n, :, 0] = bf(-1e10)
+    inputs.q[n:, :, 0] = bf(1e30)
+    mask = pytest.ev.build_block_mask([9], [21], 32, 64, 1, 8, 2, 1,
+                                      tau_p=w.tau_p)
+    assert (_gpu_coarse(w, mask, inputs=inputs) == 0).all()
+
+
 @pytest.mark.parametrize("name", list(CASES))
 def test_coarse_evidence(name):
     _check_coarse(name, CASES[name])
