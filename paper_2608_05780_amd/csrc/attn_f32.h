@@ -9,15 +9,21 @@
 // Here every
 // fp32 operand is the exact sum of three bf16 values, x = h + m + l with
 // h = RNE(x), m = RNE(x - h), l = x - h - m (8 + 8 + 8 significant bits), and
-// a product is the six partial products down to 2^-18 of it, each exact in
-// the fp32 accumulator: h h, h m, m h, m m, h l, l h. What is left out stays
-// below 2^-25 of a product, under the rounding of its accumulation, of which
-// there are fewer than on the fp32 MFMA (a bf16 step sums 16 products).
+// a product is the six partial products down to 2^-17 of it, each exact in
+// the fp32 accumulator: h h, h m, m h, m m, h l, l h. What is left out, m l,
+// l m and l l, is at most 2^-24 of the product, half an ulp (m is up to 2^-8 of
+// x, l up to 2^-17), where an fp32 product enters its accumulator exactly; in
+// return there are fewer roundings of the accumulator than on the fp32 MFMA (a
+// bf16 step sums 16 products).
 //
-// Inputs whose split is not finite (an infinity minus itself) leave NaN where
-// fp32 arithmetic may not: a wave that ends with a non-finite row sum or
-// accumulator computes its rows again with fp32 MFMA straight from global
-// memory.
+// The sum of three is exact only while the last bit of x is in bf16's range:
+// for |x| >= 2^-100 with room to spare. Probabilities go in times 2^40, so that
+// all that exp2 returns are (sums and accumulators are scaled back at the end).
+// A nonzero V below 2^-100, or a Q or K of 2^60 and more (against which an
+// inexact factor below 2^-100 could count), is marked with a NaN where it is
+// split; an infinity's split is NaN by itself. A wave that ends with a
+// non-finite row sum or accumulator computes its rows again with fp32 MFMA
+// straight from global memory.
 //
 // A key tile is taken 32 keys at a time. Its K and V rows come as fp32 by
 // direct global -> LDS loads, each thread then reads back the chunks it
@@ -27,6 +33,8 @@
 // d = 128: two work-groups share a CU, and one splits (VALU, LDS writes)
 // while the other multiplies.
 #pragma once
+#include <type_traits>
+
 #include "attn_tiles.h"
 #include "kernels.h"
 
@@ -41,6 +49,9 @@ struct F32Split {
   static constexpr int RAW = kKeys * D * 4;        // raw bytes of K or V
   static constexpr int NU = kKeys * RC / kThreads; // chunks per thread
   static constexpr int kSmem = 6 * PB + 2 * RAW;
+  static constexpr float kPScale = 0x1p40f;        // on the probabilities
+  static constexpr float kLeast = 0x1p-100f;       // V, unless 0
+  static constexpr float kMost = 0x1p60f;          // Q and K
 
   // x = p[0] + p[1] + p[2], each rounded to nearest even
   __device__ static void split(const f32x8 x, bf16x8 (&p)[3]) {
@@ -49,6 +60,30 @@ struct F32Split {
     p[1] = __builtin_convertvector(r, bf16x8);
     p[2] = __builtin_convertvector(r - __builtin_convertvector(p[1], f32x8),
                                    bf16x8);
+  }
+  // whether 8 values of Q or K, or of V, are past what the split is used for
+  __device__ static bool past_qk(const f32x4 a, const f32x4 b) {
+    float x = 0.f;
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      x = fmaxf(x, fmaxf(__builtin_fabsf(a[e]), __builtin_fabsf(b[e])));
+    return x >= kMost;
+  }
+  __device__ static bool past_v(const f32x4 a, const f32x4 b) {
+    // twice the bits less 2: without the sign, and +-0 on top
+    uint32_t x = 0xFFFFFFFFu;
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      x = min(x, min((__float_as_uint(a[e]) << 1) - 2u,
+                     (__float_as_uint(b[e]) << 1) - 2u));
+    return x < (__builtin_bit_cast(uint32_t, kLeast) << 1) - 2u;
+  }
+  // NaN in the highest part: the rows' results are not finite
+  __device__ static void poison(bf16x8 (&p)[3], bool past) {
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    u32x4 h = __builtin_bit_cast(u32x4, p[0]);
+    h[0] |= past ? 0x7FC07FC0u : 0u;
+    p[0] = __builtin_bit_cast(bf16x8, h);
   }
 };
 
@@ -98,6 +133,7 @@ __device__ __forceinline__ void attn_f32_item(const DevPlan& pl,
     const f32x4 b = *(const f32x4*)(qg + 16 * kk + 8 * g + 4);
     bf16x8 p[3];
     X::split(__builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7), p);
+    X::poison(p, X::past_qk(a, b));
 #pragma unroll
     for (int u = 0; u < 3; ++u) qf[u][kk] = p[u];
   }
@@ -136,6 +172,7 @@ __device__ __forceinline__ void attn_f32_item(const DevPlan& pl,
         const f32x4 b = *(const EV_LDS f32x4*)(src + 1024);
         bf16x8 p[3];
         X::split(__builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7), p);
+        X::poison(p, t ? X::past_v(a, b) : X::past_qk(a, b));
         const int ch =
             ccol ^ (t ? swz<kSwzV, RC>(row) : swz<kSwzK, RC>(row));
         EV_LDS char* const dst = (t ? vpl : kpl) + (row * RC + ch) * 16;
@@ -294,18 +331,22 @@ __device__ __forceinline__ void attn_f32_item(const DevPlan& pl,
     }
     m_ref = need ? m_new : m_ref;
   };
-  auto probs = [&](f32x16& s, float mu) -> float {
+  // probabilities, and with them row sums and accumulators, times 2^40 (SPLIT)
+  // or as they are (the fp32 MFMA pass)
+  auto probs = [&](f32x16& s, float mu, auto split) -> float {
     float ts = 0.f;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      s[r] = exp2_(fmaf(s[r], c2, -mu));
+      s[r] = exp2_(fmaf(s[r], c2, -mu)) * (split.value ? X::kPScale : 1.f);
       ts += s[r];
     }
     return ts;
   };
   // per-frame log2 partial masses of half c (query rows; visual rows with
   // frame cues), or the query rows' non-visual mass
-  auto evidence = [&](const f32x16& s, float ts, int c, const Tile& t) {
+  auto evidence = [&](const f32x16& s, float ts, int c, const Tile& t,
+                      auto split) {
+    constexpr float kUnit = split.value ? 1.f / X::kPScale : 1.f;
     if (!is_text && !vis_ff) return;
     const float mu = m_ref == neg_inf() ? 0.f : m_ref;
     if (t.region == kVis) {
@@ -316,7 +357,7 @@ __device__ __forceinline__ void attn_f32_item(const DevPlan& pl,
         fr_part = c ? fr_part + ts : ts;
         if (c) {
           const float f = pair_sum(fr_part);
-          if (g == 0 && qvalid) *dst = mu + log2_(f);
+          if (g == 0 && qvalid) *dst = mu + log2_(f * kUnit);
         }
       } else {
         float g4[4];
@@ -331,7 +372,7 @@ __device__ __forceinline__ void attn_f32_item(const DevPlan& pl,
 #pragma unroll
           for (int q = 0; q < 4; ++q) f += (q >> lg) == si ? g4[q] : 0.f;
           if (g == 0 && qvalid && 32 * c + si * pl.Nv < t.len)
-            dst[(c * nseg + si) * dstride] = mu + log2_(f);
+            dst[(c * nseg + si) * dstride] = mu + log2_(f * kUnit);
         }
       }
     } else if (is_text) {
@@ -418,8 +459,8 @@ __device__ __forceinline__ void attn_f32_item(const DevPlan& pl,
     bool exact = __any(m_ref == neg_inf());
     float ts = 0.f;
     if (!exact) {
-      ts = probs(s, kept ? m_ref : __builtin_inff());
-      exact = __any(!(ts <= kFastBound));
+      ts = probs(s, kept ? m_ref : __builtin_inff(), std::true_type{});
+      exact = __any(!(ts <= kFastBound * X::kPScale));
       if (exact) {
         qk_half(s);
         mask_half(s, c, t);
@@ -427,10 +468,10 @@ __device__ __forceinline__ void attn_f32_item(const DevPlan& pl,
     }
     if (exact) {
       half_ref(s, kept);
-      ts = probs(s, m_ref == neg_inf() ? 0.f : m_ref);
+      ts = probs(s, m_ref == neg_inf() ? 0.f : m_ref, std::true_type{});
     }
     l_part += ts;
-    evidence(s, ts, c, t);
+    evidence(s, ts, c, t, std::true_type{});
     pv_half(s);
   };
 
@@ -472,12 +513,14 @@ __device__ __forceinline__ void attn_f32_item(const DevPlan& pl,
   if (!active) return;
 
   // ---- rows with a non-finite result: again in fp32 throughout
+  float unit = 1.f / X::kPScale;
   float chk = l_part - l_part;
 #pragma unroll
   for (int i = 0; i < NMT; ++i)
 #pragma unroll
     for (int r = 0; r < 16; ++r) chk += o[i][r] - o[i][r];
   if (__any(qvalid && chk != 0.f)) {
+    unit = 1.f;
     m_ref = neg_inf();
     l_part = nv_part = fr_part = 0.f;
 #pragma unroll
@@ -502,9 +545,10 @@ __device__ __forceinline__ void attn_f32_item(const DevPlan& pl,
         }
         mask_half(s, c, d);
         half_ref(s, kept);
-        const float ts = probs(s, m_ref == neg_inf() ? 0.f : m_ref);
+        const float ts =
+            probs(s, m_ref == neg_inf() ? 0.f : m_ref, std::false_type{});
         l_part += ts;
-        evidence(s, ts, c, d);
+        evidence(s, ts, c, d, std::false_type{});
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           const int key = min(32 * c + 8 * (r >> 2) + 4 * g + (r & 3),
@@ -520,10 +564,10 @@ __device__ __forceinline__ void attn_f32_item(const DevPlan& pl,
   }
 
   // ---- outputs, straight from the lanes' rows
-  const float l_tot = pair_sum(l_part), nv_tot = pair_sum(nv_part);
+  const float l_tot = pair_sum(l_part) * unit, nv_tot = pair_sum(nv_part) * unit;
   if (!qvalid) return;
   if (!is_text) {
-    const float inv = 1.f / l_tot;
+    const float inv = unit / l_tot;
 #pragma unroll
     for (int mt = 0; mt < NMT; ++mt)
 #pragma unroll
@@ -545,8 +589,9 @@ __device__ __forceinline__ void attn_f32_item(const DevPlan& pl,
     for (int mt = 0; mt < NMT; ++mt)
 #pragma unroll
       for (int r4 = 0; r4 < 4; ++r4) {
-        const f32x4 v = {o[mt][4 * r4], o[mt][4 * r4 + 1], o[mt][4 * r4 + 2],
-                         o[mt][4 * r4 + 3]};
+        const f32x4 v = {o[mt][4 * r4] * unit, o[mt][4 * r4 + 1] * unit,
+                         o[mt][4 * r4 + 2] * unit,
+                         o[mt][4 * r4 + 3] * unit};
         *(f32x4*)(po + 32 * mt + 8 * r4 + 4 * g) = v;
       }
     if (g == 0) {
