@@ -1,7 +1,8 @@
 """Aggregation over layers and heads (evisel_frame_evidence) at the sizes
 where its kernels' tiles end, against the oracle's formulas: frame counts
 around the 64-frame groups and the 4,096-score chunks of the top-k, ties, NaN
-and -inf scores, layer counts around the seven-layer groups of E_ff."""
+and -inf scores, layer counts around the four-layer groups of E_ff, head counts
+with and without each group of the head loop (16, 8, 4, 2, 1)."""
 import numpy as np
 import pytest
 
@@ -21,6 +22,10 @@ CASES = {   # frames per video, k per video, layers, heads
     "groups": ((63, 64, 65, 1, 130), (5, 64, 0, 9, 130), 8, 4),
     "chunks": ((4095, 4097, 4161), (300, -3, 5000), 1, 1),
     "layers_15": ((40,), (7,), 15, 28),
+    "layers_3_heads_31": ((70, 9), (7, 3), 3, 31),
+    "layers_4_heads_12": ((33,), (4,), 4, 12),
+    "layers_5_heads_34": ((65,), (65,), 5, 34),
+    "layers_33_heads_17": ((20, 66), (2, 8), 33, 17),
     # no video past 64 frames: means and ranks in one work-group per video
     "short_videos": ((64, 33, 1, 32, 31), (5, 40, 1, 0, 31), 35, 4),
 }
