@@ -36,6 +36,7 @@
 //                top-p attention pass (tiles that no row of a work item
 //                retained are skipped and write nothing).
 #include <algorithm>
+#include <type_traits>
 
 #include "kernels.h"
 
@@ -753,21 +754,31 @@ __global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(
 // lane's registers). The grid is small (a few hundred work-groups whatever
 // the history), so latency bounds it: 16 waves share a work-group's
 // affinity tiles and every row is searched at once, its bounds in scalar
-// registers. The whole call (means, this kernel, the reduction) takes 26.5 us
-// on 256 frames x 64 tokens + 128 query tokens and 46.7 us on 1,024 frames
-// (28/4 heads, d = 128, bf16), against 183 us and 3.6 ms when the retention
-// of every row was decided first. The per-block masses of the pass's rows are summed in row order
-// into cpart; coarse_reduce_kernel adds a video's blocks and passes in order
-// and spreads each block's mass evenly over its frames (frames never cross
-// blocks).
+// registers. The whole call (means, this kernel, the reduction) takes 27 us on
+// 256 frames x 64 tokens + 128 query tokens and 49 us on 1,024 frames (28/4
+// heads, d = 128, bf16), against 177 us and 3.6 ms when the retention of every
+// row was decided first. The per-block masses of the pass's rows are summed in
+// row order into cpart; coarse_reduce_kernel adds a video's blocks and passes in
+// order and spreads each block's mass evenly over its frames (frames never
+// cross blocks).
 constexpr int kCoarseThreads = 1024;
 constexpr int kCoarseWaves = kCoarseThreads / 64;
 constexpr int kCoarseRows = kCoarseWaves;                  // rows per pass
 constexpr int kCoarseVals = 32;                            // blocks per lane
 constexpr int kCoarsePasses = kTile64 / kCoarseRows;
-// The last waves take the E_i tiles, the others the affinity tiles.
-constexpr int kCoarseExact = 2;
-constexpr int kCoarseAff = kCoarseWaves - kCoarseExact;
+// The last waves take the E_i tiles, the others the affinity tiles (16 history
+// blocks; fp32: 32), by the tiles' number: a prefix of 16,000 tokens before 16
+// frames x 64 tokens + 128 query tokens (28/4 heads, d = 128, bf16) is 250
+// tiles against one. That call takes 131 us (255 with two waves for E_i whatever
+// the prefix, 151 with the retention of every row and four waves), 2,000 tokens
+// before 256 frames 41 us (55, 192). An E_i tile counted as 2, 3 or 5 affinity
+// tiles: 1 to 4 us more on the latter, the same elsewhere.
+__device__ __forceinline__ int coarse_exact_waves(int n_exact, int n_aff) {
+  const int all = n_exact + n_aff;
+  const int share = (kCoarseWaves * n_exact + all / 2) / all;
+  return min(n_exact, max(1, min(share, kCoarseWaves - 1)));
+}
+static_assert(kCoarseRows == 16, "the MFMA tiles are 16 rows");
 static_assert(kMaxItemCandidates <= 64 * kCoarseVals,
               "a row's share of the longest history fits its registers");
 // LDS floats of a row: its history in tiles of 16, and a bank offset.
@@ -775,101 +786,104 @@ __host__ __device__ inline int coarse_stride(int nh) {
   return ((nh + 15) & ~15) + 4;
 }
 
-__device__ __forceinline__ float pair_max_(float x) {
-  auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x),
-                                            __float_as_uint(x), false, false);
-  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+// Over the four lanes of equal lane % 16.
+__device__ __forceinline__ float rows_max(float x) {
+  return __uint_as_float(
+      cross_rows(__float_as_uint(x), [](unsigned a, unsigned b) {
+        return __float_as_uint(fmaxf(__uint_as_float(a), __uint_as_float(b)));
+      }));
 }
-__device__ __forceinline__ float pair_sum_(float x) {
-  auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x),
-                                            __float_as_uint(x), false, false);
-  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+__device__ __forceinline__ float rows_sum(float x) {
+  return __uint_as_float(
+      cross_rows(__float_as_uint(x), [](unsigned a, unsigned b) {
+        return __float_as_uint(__uint_as_float(a) + __uint_as_float(b));
+      }));
 }
 
-// Log2 max and sum of row r0 + l32's exact logits over the E_i tiles e =
-// ph, ph + kCoarseExact, ... (system-prefix blocks, then the row's own block).
+// Log2 max and sum of the exact logits of row r0 + lane % 16 over the E_i
+// tiles e = ph, ph + n_waves, ... (system-prefix blocks, then the row's own
+// block), on 16x16 MFMA as in coarse_affinities: a load instruction reads 64
+// bytes of each of 16 key rows (32x32 tiles, half of whose rows would be
+// empty, read 32 or 16 bytes, and many waves then miss the L1). The operands
+// of the next kBuf groups of 16 keys are in flight.
 template <bool F32, int D>
 __device__ __forceinline__ void exact_part(
-    const DevPlan& pl, const SelCall& sc, const BlockDesc& qb, int h, int kvh, int sys0, int nsys, int r0, int ph, int lane, float& mw,
+    const DevPlan& pl, const SelCall& sc, const BlockDesc& qb, int h, int kvh,
+    int sys0, int nsys, int r0, int ph, int n_waves, int lane, float& mw,
     float& lw) {
-  const int l32 = lane & 31, g = lane >> 5;
-  const bool rv = l32 < kCoarseRows && r0 + l32 < qb.len;
-  const int qtok = qb.start + r0 + l32;
-  const size_t qoff = ((size_t)(rv ? qtok : qb.start) * pl.hq + h) * D;
-  mw = -__builtin_inff();
+  using T = std::conditional_t<F32, float, __bf16>;
+  using Vec = std::conditional_t<F32, f32x4, bf16x8>;
+  constexpr int VL = F32 ? 4 : 8, KS = D / (4 * VL), NG = kTile64 / 16;
+  constexpr int kBuf = F32 && D == 128 ? 2 : 4;   // what the registers hold
+  const int i16 = lane & 15, kg = lane >> 4;
+  const bool rv = r0 + i16 < qb.len;
+  const int qtok = qb.start + min(r0 + i16, qb.len - 1);
+  const T* const qr = (const T*)sc.q + ((size_t)qtok * pl.hq + h) * D + VL * kg;
+  Vec qf[KS], kf[kBuf][KS];
+#pragma unroll
+  for (int u = 0; u < KS; ++u) qf[u] = *(const Vec*)(qr + 4 * VL * u);
+  auto tile = [&](int e) { return e < nsys ? pl.blocks[sys0 + e] : qb; };
+  auto load = [&](const BlockDesc& kb, int c) {   // group c of tile kb
+    const int key = kb.start + min(16 * c + i16, kb.len - 1);
+    const T* const p =
+        (const T*)sc.k + ((size_t)key * pl.hkv + kvh) * D + VL * kg;
+#pragma unroll
+    for (int u = 0; u < KS; ++u)
+      kf[c % kBuf][u] = *(const Vec*)(p + 4 * VL * u);
+  };
+  mw = neg_inf();
   lw = 0.f;
-  for (int e = ph; e <= nsys; e += kCoarseExact) {
-    const BlockDesc kb = e < nsys ? pl.blocks[sys0 + e] : qb;
-    f32x16 s[2] = {f32x16{}, f32x16{}};
-    const int key0 = min(l32, kb.len - 1), key1 = min(32 + l32, kb.len - 1);
-    const size_t ko0 = ((size_t)(kb.start + key0) * pl.hkv + kvh) * D;
-    const size_t ko1 = ((size_t)(kb.start + key1) * pl.hkv + kvh) * D;
-    if (!F32) {
-      // both halves' operands in flight at once (one round trip to memory)
-      constexpr int KS = D / 16;
-      const __bf16* const ks = (const __bf16*)sc.k + 8 * g;
-      const __bf16* const qs = (const __bf16*)sc.q + qoff + 8 * g;
-      bf16x8 qf[KS], k0[KS], k1[KS];
+  BlockDesc kb = tile(ph);
 #pragma unroll
-      for (int kk = 0; kk < KS; ++kk) {
-        qf[kk] = *(const bf16x8*)(qs + 16 * kk);
-        k0[kk] = *(const bf16x8*)(ks + ko0 + 16 * kk);
-      }
+  for (int c = 0; c < kBuf; ++c) load(kb, c);
+  for (int e = ph; e <= nsys; e += n_waves) {
+    const bool more = e + n_waves <= nsys;
+    const BlockDesc nx = tile(min(e + n_waves, nsys));
+    float x[4 * NG];
 #pragma unroll
-      for (int kk = 0; kk < KS; ++kk)
-        k1[kk] = *(const bf16x8*)(ks + ko1 + 16 * kk);
-      __builtin_amdgcn_sched_barrier(0);
+    for (int c = 0; c < NG; ++c) {
+      f32x4 acc = {};
 #pragma unroll
-      for (int kk = 0; kk < KS; ++kk) {
-        s[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k0[kk], qf[kk], s[0], 0,
+      for (int u = 0; u < KS; ++u) {
+        const Vec k = kf[c % kBuf][u];
+        if constexpr (F32) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(k[i], qf[u][i], acc, 0,
                                                        0, 0);
-        s[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k1[kk], qf[kk], s[1], 0,
-                                                       0, 0);
-      }
-    } else {
-      const float* const ks = (const float*)sc.k + g * (D / 2);
-      const float* const qs = (const float*)sc.q + qoff + g * (D / 2);
-#pragma unroll
-      for (int u = 0; u < D / 8; ++u) {
-        const f32x4 qv = *(const f32x4*)(qs + 4 * u);
-        const f32x4 a = *(const f32x4*)(ks + ko0 + 4 * u);
-        const f32x4 b = *(const f32x4*)(ks + ko1 + 4 * u);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          s[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[e], qv[e], s[0], 0, 0,
-                                                      0);
-          s[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(b[e], qv[e], s[1], 0, 0,
-                                                      0);
+        } else {
+          acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k, qf[u], acc, 0, 0, 0);
         }
       }
-    }
-    float mt = -__builtin_inff();
+      if (c + kBuf < NG)
+        load(kb, c + kBuf);
+      else if (more)
+        load(nx, c + kBuf - NG);
 #pragma unroll
-    for (int c = 0; c < 2; ++c)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int key = 32 * c + 8 * (r >> 2) + 4 * g + (r & 3);
+      for (int i = 0; i < 4; ++i) {
+        const int key = 16 * c + 4 * kg + i;
         const bool ok = rv && key < kb.len && kb.start + key <= qtok;
-        s[c][r] = ok ? s[c][r] * sc.scale_log2 : -__builtin_inff();
-        mt = fmaxf(mt, s[c][r]);
+        x[4 * c + i] = ok ? acc[i] * sc.scale_log2 : neg_inf();
       }
-    mt = pair_max_(mt);
-    const float mn = fmaxf(mw, mt);
-    if (mn == -__builtin_inff()) continue;
-    float t = 0.f;
+    }
+    float mt = neg_inf();
 #pragma unroll
-    for (int c = 0; c < 2; ++c)
+    for (int i = 0; i < 4 * NG; ++i) mt = fmaxf(mt, x[i]);
+    const float mn = fmaxf(mw, rows_max(mt));
+    if (mn != neg_inf()) {
+      float t = 0.f;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) t += __builtin_amdgcn_exp2f(s[c][r] - mn);
-    t = pair_sum_(t);
-    lw = (mw == -__builtin_inff() ? 0.f : lw * __builtin_amdgcn_exp2f(mw - mn))
-         + t;
-    mw = mn;
+      for (int i = 0; i < 4 * NG; ++i) t += __builtin_amdgcn_exp2f(x[i] - mn);
+      lw = (mw == neg_inf() ? 0.f : lw * __builtin_amdgcn_exp2f(mw - mn)) +
+           rows_sum(t);
+      mw = mn;
+    }
+    kb = nx;
   }
 }
 
 // Affinities of the pass's 16 query rows (bf16) against history blocks
-// 16 t .. 16 t + 15 for t = wave, wave + kCoarseAff, ..., to ev[row * stride +
+// 16 t .. 16 t + 15 for t = wave, wave + n_waves, ..., to ev[row * stride +
 // block] (blocks past the history get -inf): 16x16x32 MFMA, kbar = hi + lo, the
 // next tile's operands in flight while one is multiplied. The first tile's
 // come with the query rows.
@@ -877,7 +891,7 @@ template <int D>
 __device__ __forceinline__ void coarse_affinities(
     const DevPlan& pl, const void* kbar, const void* q, float scale_log2,
     const BlockDesc& qb, int h, int kvh, int first, int nh, int r0, int wave,
-    float* ev, int stride, int lane) {
+    int n_waves, float* ev, int stride, int lane) {
   constexpr int KS = D / 32;
   const int i16 = lane & 15, kg = lane >> 4;
   const int ntile = (nh + 15) / 16;
@@ -901,14 +915,14 @@ __device__ __forceinline__ void coarse_affinities(
   bf16x8 qf[KS];
 #pragma unroll
   for (int u = 0; u < KS; ++u) qf[u] = *(const bf16x8*)(qr + 32 * u);
-  for (int t = wave; t < ntile; t += kCoarseAff) {
+  for (int t = wave; t < ntile; t += n_waves) {
     bf16x8 ch[KS], cl[KS];
 #pragma unroll
     for (int u = 0; u < KS; ++u) {
       ch[u] = kh[u];
       cl[u] = kl[u];
     }
-    if (t + kCoarseAff < ntile) load(t + kCoarseAff);
+    if (t + n_waves < ntile) load(t + n_waves);
     f32x4 acc = {};
 #pragma unroll
     for (int u = 0; u < KS; ++u) {
@@ -946,28 +960,32 @@ __global__ __launch_bounds__(kCoarseThreads) void coarse_kernel(
   }
   const int stride = coarse_stride(nh);
   float* const ev = dyn;                      // [RPW][stride]
-  float* const emx = dyn + RPW * stride;      // [exact waves][32 rows]
-  float* const esm = emx + kCoarseExact * 32;
+  float* const emx = dyn + RPW * stride;      // [exact waves][rows]
+  float* const esm = emx + kCoarseWaves * RPW;
   const int kvh = h / (pl.hq / pl.hkv);
   const int first = qbid - nh;                // first visual block
   const SeqDesc sq = pl.seqs[tt.seq];
   const int nsys = (sq.vis0 - sq.tok0 + kTile64 - 1) / kTile64;
-  if (wave < kCoarseAff) {
+  constexpr int kAffCols = F32 ? 32 : 16;     // history blocks per tile
+  const int n_exact = coarse_exact_waves(nsys + 1,
+                                         (nh + kAffCols - 1) / kAffCols);
+  const int n_aff = kCoarseWaves - n_exact;
+  if (wave < n_aff) {
     if (F32)
       affinity_tiles<F32, D>(pl, ws.kbar, sc.q, sc.scale_log2, qb, h, kvh,
-                             first, nh, nh, r0, RPW, 0, wave, kCoarseAff,
-                             ev, stride, lane, nullptr);
+                             first, nh, nh, r0, RPW, 0, wave, n_aff, ev, stride,
+                             lane, nullptr);
     else
       coarse_affinities<D>(pl, ws.kbar, sc.q, sc.scale_log2, qb, h, kvh, first,
-                           nh, r0, wave, ev, stride, lane);
+                           nh, r0, wave, n_aff, ev, stride, lane);
   } else {
-    const int e0 = wave - kCoarseAff;
+    const int e0 = wave - n_aff;
     float mw, lw;
-    exact_part<F32, D>(pl, sc, qb, h, kvh, first - nsys, nsys, r0, e0, lane, mw,
-                       lw);
-    if ((lane >> 5) == 0) {
-      emx[e0 * 32 + lane] = mw;
-      esm[e0 * 32 + lane] = lw;
+    exact_part<F32, D>(pl, sc, qb, h, kvh, first - nsys, nsys, r0, e0, n_exact,
+                       lane, mw, lw);
+    if (lane < RPW) {
+      emx[e0 * RPW + lane] = mw;
+      esm[e0 * RPW + lane] = lw;
     }
   }
   __syncthreads();
@@ -976,12 +994,12 @@ __global__ __launch_bounds__(kCoarseThreads) void coarse_kernel(
     // The row's history, block 64 i + lane in v[i]: e_j = exp2(g_j - max),
     // and the cut t* by a bisection over the bit patterns as in
     // retain_row_regs, on the mass that is dropped: t* is the largest value
-    // below which at most (1 - tau) Z lies. That mass is a few per cent of Z,
-    // so its fp32 sum rounds correspondingly less than the kept mass would
-    // and fewer cuts fall within rounding (on the kept mass 25.5 and 44.0 us). Every bound is uniform over the
-    // wave, and the entries at or above a pivot are counted from the compare
-    // masks by the scalar unit, so a pass is three vector instructions per
-    // entry and the sum over the lanes.
+    // below which at most (1 - tau) Z lies. At the usual tau that mass is a few
+    // per cent of Z, so its fp32 sum rounds correspondingly less than the kept
+    // mass would and fewer cuts fall within rounding. Every bound is uniform
+    // over the wave, and the entries at or above a pivot are counted from the
+    // compare masks by the scalar unit, so a pass is three vector instructions
+    // per entry and the sum over the lanes.
     float* const my = ev + wave * stride;
     const int ni = (nh + 63) >> 6;
     float v[kCoarseVals];
@@ -1043,10 +1061,10 @@ __global__ __launch_bounds__(kCoarseThreads) void coarse_kernel(
            cum += __uint_as_float(lo))
         --take;
     int before = 0;   // entries at the cut in lower blocks
-    // E_i: the two waves' parts
+    // E_i: the waves' parts, in order
     float mE = -__builtin_inff(), lE = 0.f;
-    for (int w = 0; w < kCoarseExact; ++w) {
-      const float m = emx[w * 32 + wave], l = esm[w * 32 + wave];
+    for (int w = 0; w < n_exact; ++w) {
+      const float m = emx[w * RPW + wave], l = esm[w * RPW + wave];
       if (m == -__builtin_inff()) continue;
       const float mn = fmaxf(mE, m);
       lE = (mE == -__builtin_inff() ? 0.f
@@ -1216,7 +1234,7 @@ hipError_t launch_coarse(const DevPlan& p, const Workspace& w,
     const int nh_max = std::max(p.hmax, 1);
     const size_t lds =
         (size_t)kCoarseRows * coarse_stride(nh_max) * 4 +
-        2 * kCoarseExact * 32 * 4;
+        2 * kCoarseWaves * kCoarseRows * 4;
     dim3 grid(p.n_tiles, p.hq, kCoarsePasses), block(kCoarseThreads);
     auto go = [&](auto fn) -> hipError_t {
       if (lds > 64 * 1024) {

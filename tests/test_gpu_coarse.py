@@ -54,10 +54,10 @@ CASES = {
 }
 
 
-# The query rows' histories at the edges of a lane's share (64 lanes per row,
-# shares in steps of four blocks): one block, a full step and one past it, a
-# short last visual block, and the longest history a mask accepts (2,047
-# blocks, with one to spare for the row's own).
+# The query rows' histories at the edges of a wave's share (one row per wave, a
+# block per lane, four steps of 64 blocks at a time): one block, one group of
+# steps and the next, a short last visual block, and the longest history a mask
+# accepts (2,047 blocks, with one to spare for the row's own).
 EDGES = {
     "one_block": _w("one-block", n_frames=(1,), n_text=(3,), n_sys=(0,),
                     plant_args={"count": 1, "s_frame": (2.0, 3.0),
@@ -71,6 +71,23 @@ EDGES = {
                        n_sys=(130,)),
     "longest": _w("longest", d=64, hq=2, tokens_per_frame=64,
                   n_frames=(2046,), n_text=(70,), n_sys=(0,)),
+}
+
+
+# System prefixes: their blocks and the history's share a work-group's 16 waves
+# by number (at least one each), both with one tile and with many.
+PREFIX = {
+    "one_each": _w("one-each", n_frames=(4,), n_text=(17,), n_sys=(64,)),
+    "waves_15": _w("waves-15", hq=2, hkv=1, n_frames=(4,), n_text=(65,),
+                   n_sys=(961,)),
+    "long": _w("long-prefix", hq=2, hkv=1, tokens_per_frame=16, n_frames=(5,),
+               n_text=(70,), n_sys=(4159,)),
+    "shared_d64": _w("shared-d64", d=64, hq=2, hkv=1, tokens_per_frame=64,
+                     n_frames=(300,), n_text=(20,), n_sys=(1100,)),
+    "fp32_long": _w("fp32-long", dtype="fp32", hq=2, hkv=1, n_frames=(3,),
+                    n_text=(33,), n_sys=(2050,)),
+    "fp32_d64": _w("fp32-prefix-d64", dtype="fp32", d=64, hq=2, hkv=1,
+                   n_frames=(70,), n_text=(64,), n_sys=(300,)),
 }
 
 
@@ -95,6 +112,11 @@ def _gpu_coarse(w, mask, l=0, inputs=None):
 @pytest.mark.parametrize("name", list(EDGES))
 def test_coarse_evidence_history_edges(name):
     _check_coarse(name, EDGES[name])
+
+
+@pytest.mark.parametrize("name", list(PREFIX))
+def test_coarse_evidence_system_prefix(name):
+    _check_coarse(name, PREFIX[name])
 
 
 @pytest.mark.parametrize("name", ["share_4", "share_8_short", "fp32_share_8"])
