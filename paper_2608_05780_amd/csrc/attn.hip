@@ -528,22 +528,21 @@ attn_kernel(const DevPlan pl, const Workspace ws, const AttnCall ac) {
 // saved), summed over the kv head's query heads. The K tile is staged in
 // LDS once; waves 0-1 take the even heads of each head pair, waves 2-3 the
 // odd ones, the next pair's Q and LSE are fetched while the current pair is
-// computed, and the two wave groups' sums are added in a fixed order. The
-// result is a partial per kv head; cue_finish_kernel adds the kv heads in order
+// computed, and the two wave groups' sums are added in a fixed order (fp32:
+// intra_f32_part). The result is a partial per kv head; cue_finish_kernel adds the kv heads in order
 // and divides by Hq.
 template <class P, int D>
 __global__ __attribute__((amdgpu_flat_work_group_size(kThreads, kThreads)))
 void intra_kernel(const DevPlan pl, const Workspace ws, const AttnCall ac) {
   using T = typename P::T;
+  constexpr bool F32 = sizeof(T) == 4;
   constexpr int TB = kTile * P::RC * 16;
   constexpr int RB = 2 * 64 * 32 * 4;              // wave-pair hand-off
   // bf16: the key tile, then both heads' query rows of the current pair
-  // (staged like a key tile); fp32 rows are read from global memory
-  constexpr bool kStageQ = sizeof(T) == 2;
-  constexpr int SM = kStageQ ? 3 * TB : (TB > RB ? TB : RB);
+  // (staged like a key tile); fp32: the key tile's planes
+  constexpr int SM = F32 ? 6 * F32Split<D>::PB : 3 * TB;
   static_assert(SM >= RB, "hand-off buffer");
   __shared__ __attribute__((aligned(1024))) char smem[SM];
-  EV_LDS char* kt = (EV_LDS char*)smem;
   const BlockDesc qb = pl.blocks[blockIdx.x];
   if (qb.region != kVis) return;
   const int kvh = blockIdx.y;
@@ -554,38 +553,36 @@ void intra_kernel(const DevPlan pl, const Workspace ws, const AttnCall ac) {
   const bool qvalid = qrow < qb.len;
   const int qpos = qb.start + qrow;
   const int Nv = pl.Nv;
-  const int group = pl.hq / pl.hkv;
-  const int npair = (group + 1) / 2;
-  const float c2 = ac.scale_log2;
-  TileLoader<T, D, kSwzK> kload;
-  kload.init(pl.hkv, wave, lane);
-  kload.issue(kt, (const T*)ac.k, qb.start, qb.len, kvh, wave);
-
   f32x16 acc[2] = {f32x16{}, f32x16{}};
-  // head of pair pi for this wave (or -1 past an odd group's end)
-  auto head = [&](int pi) {
-    const int hi = 2 * pi + (wave >> 1);
-    return pi < npair && hi < group ? kvh * group + hi : -1;
-  };
-  auto fetch = [&](typename P::QFrag& qf, float& l2, int h) {
-    if (h < 0) return;
-    P::load_q(qf, ac.q, qpos, qvalid, h, pl.hq, g);
-    l2 = qvalid ? ws.lse2v[(size_t)h * pl.S + qpos] : 0.f;
-  };
-  auto accumulate = [&](const typename P::QFrag& qf, float l2, int h) {
-    if (h < 0) return;
-    f32x16 s[2] = {f32x16{}, f32x16{}};
-    P::qk(s, kt, qf, l32, g);
+  if constexpr (F32) {
+    intra_f32_part<D>(pl, ws, ac, qb, kvh, tid, wave, smem, acc);
+  } else {
+    EV_LDS char* kt = (EV_LDS char*)smem;
+    const int group = pl.hq / pl.hkv;
+    const int npair = (group + 1) / 2;
+    const float c2 = ac.scale_log2;
+    TileLoader<T, D, kSwzK> kload;
+    kload.init(pl.hkv, wave, lane);
+    kload.issue(kt, (const T*)ac.k, qb.start, qb.len, kvh, wave);
+
+    // head of pair pi for this wave (or -1 past an odd group's end)
+    auto head = [&](int pi) {
+      const int hi = 2 * pi + (wave >> 1);
+      return pi < npair && hi < group ? kvh * group + hi : -1;
+    };
+    auto accumulate = [&](const typename P::QFrag& qf, float l2, int h) {
+      if (h < 0) return;
+      f32x16 s[2] = {f32x16{}, f32x16{}};
+      P::qk(s, kt, qf, l32, g);
 #pragma unroll
-    for (int c = 0; c < 2; ++c)
+      for (int c = 0; c < 2; ++c)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int kl = 32 * c + 8 * (r >> 2) + 4 * g + (r & 3);
-        const bool ok = qvalid && kl <= qrow && kl / Nv == qrow / Nv;
-        acc[c][r] += ok ? exp2_(fmaf(s[c][r], c2, -l2)) : 0.f;
-      }
-  };
-  if constexpr (kStageQ) {
+        for (int r = 0; r < 16; ++r) {
+          const int kl = 32 * c + 8 * (r >> 2) + 4 * g + (r & 3);
+          const bool ok = qvalid && kl <= qrow && kl / Nv == qrow / Nv;
+          acc[c][r] += ok ? exp2_(fmaf(s[c][r], c2, -l2)) : 0.f;
+        }
+    };
     // pair pi's query rows: head 2 pi + s of the group to slot s, in whole
     // 16-byte chunks of each row; wave w reads slot w / 2
     EV_LDS char* qs = kt + TB;
@@ -612,18 +609,6 @@ void intra_kernel(const DevPlan pl, const Workspace ws, const AttnCall ac) {
       __syncthreads();                             // the slots may refill
       stage(pi + 1);
       accumulate(qf, l2, h);
-    }
-  } else {
-    typename P::QFrag qa, qb2;
-    float la = 0.f, lb = 0.f;
-    fetch(qa, la, head(0));
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();                               // K tile in LDS
-    for (int pi = 0; pi < npair; pi += 2) {
-      fetch(qb2, lb, head(pi + 1));
-      accumulate(qa, la, head(pi));
-      fetch(qa, la, head(pi + 2));
-      accumulate(qb2, lb, head(pi + 1));
     }
   }
   // waves 2-3 hand their sums to waves 0-1 through LDS (lane-contiguous)

@@ -85,6 +85,46 @@ struct F32Split {
     h[0] |= past ? 0x7FC07FC0u : 0u;
     p[0] = __builtin_bit_cast(bf16x8, h);
   }
+  // 8 values of Q or K
+  __device__ static void split_qk(const f32x4 a, const f32x4 b,
+                                  bf16x8 (&p)[3]) {
+    split(__builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7), p);
+    poison(p, past_qk(a, b));
+  }
+  // The lane's operand of step kk from the planes of 32 K rows.
+  __device__ static void k_read(const EV_LDS char* kpl, int l32, int g, int kk,
+                                bf16x8 (&f)[3]) {
+    const EV_LDS char* a =
+        kpl + (l32 * RC + ((2 * kk + g) ^ swz<kSwzK, RC>(l32))) * 16;
+#pragma unroll
+    for (int q = 0; q < 3; ++q) f[q] = *(const EV_LDS bf16x8*)(a + q * PB);
+  }
+  // One step's six partial products; the logits are hi + lo.
+  __device__ static void qk_step(const bf16x8 (&f)[3], const bf16x8 q0,
+                                 const bf16x8 q1, const bf16x8 q2, f32x16& lo,
+                                 f32x16& hi) {
+    mm(f[2], q0, lo);
+    mm(f[1], q1, lo);
+    mm(f[0], q2, lo);
+    mm(f[1], q0, lo);
+    mm(f[0], q1, lo);
+    mm(f[0], q0, hi);
+  }
+  __device__ static void mm(bf16x8 x, bf16x8 y, f32x16& c) {
+    c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, y, c, 0, 0, 0);
+  }
+  // The same logits with fp32 MFMA, from the lane's K and Q rows in memory.
+  __device__ static void qk_f32(const float* kr, const float* qr, int g,
+                                f32x16& s) {
+    s = f32x16{};
+    for (int u = 0; u < D / 8; ++u) {
+      const f32x4 a = *(const f32x4*)(kr + g * (D / 2) + 4 * u);
+      const f32x4 b = *(const f32x4*)(qr + g * (D / 2) + 4 * u);
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        s = __builtin_amdgcn_mfma_f32_32x32x2f32(a[e], b[e], s, 0, 0, 0);
+    }
+  }
 };
 
 template <int D, bool TOPP>
@@ -132,8 +172,7 @@ __device__ __forceinline__ void attn_f32_item(const DevPlan& pl,
     const f32x4 a = *(const f32x4*)(qg + 16 * kk + 8 * g);
     const f32x4 b = *(const f32x4*)(qg + 16 * kk + 8 * g + 4);
     bf16x8 p[3];
-    X::split(__builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7), p);
-    X::poison(p, X::past_qk(a, b));
+    X::split_qk(a, b, p);
 #pragma unroll
     for (int u = 0; u < 3; ++u) qf[u][kk] = p[u];
   }
@@ -385,29 +424,14 @@ __device__ __forceinline__ void attn_f32_item(const DevPlan& pl,
   Bf16Path<D>::pv_offsets(pvo, lane);
   // (the operands of a step are read during the step before; the barriers
   // keep the scheduler from reading further ahead than the registers allow)
-  auto mm = [](bf16x8 x, bf16x8 y, f32x16& c) {
-    c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, y, c, 0, 0, 0);
-  };
-  auto k_read = [&](bf16x8 (&f)[3], int kk) {
-    const EV_LDS char* a =
-        kpl + (l32 * RC + ((2 * kk + g) ^ swz<kSwzK, RC>(l32))) * 16;
-#pragma unroll
-    for (int q = 0; q < 3; ++q) f[q] = *(const EV_LDS bf16x8*)(a + q * PB);
-  };
   auto qk_half = [&](f32x16& s) {
     f32x16 lo = {}, hi = {};
     bf16x8 kf[2][3];
-    k_read(kf[0], 0);
+    X::k_read(kpl, l32, g, 0, kf[0]);
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk) {
-      if (kk + 1 < KK) k_read(kf[(kk + 1) & 1], kk + 1);
-      const bf16x8(&f)[3] = kf[kk & 1];
-      mm(f[2], qf[0][kk], lo);
-      mm(f[1], qf[1][kk], lo);
-      mm(f[0], qf[2][kk], lo);
-      mm(f[1], qf[0][kk], lo);
-      mm(f[0], qf[1][kk], lo);
-      mm(f[0], qf[0][kk], hi);
+      if (kk + 1 < KK) X::k_read(kpl, l32, g, kk + 1, kf[(kk + 1) & 1]);
+      X::qk_step(kf[kk & 1], qf[0][kk], qf[1][kk], qf[2][kk], lo, hi);
       __builtin_amdgcn_sched_barrier(0);
     }
     s = hi + lo;
@@ -440,12 +464,12 @@ __device__ __forceinline__ void attn_f32_item(const DevPlan& pl,
       const int ks = i / NMT, mt = i % NMT;
       if (i + 1 < 2 * NMT) v_read(vf[(i + 1) & 1], (i + 1) / NMT, (i + 1) % NMT);
       const bf16x8(&f)[3] = vf[i & 1];
-      mm(f[2], pb[ks][0], o[mt]);
-      mm(f[1], pb[ks][1], o[mt]);
-      mm(f[0], pb[ks][2], o[mt]);
-      mm(f[1], pb[ks][0], o[mt]);
-      mm(f[0], pb[ks][1], o[mt]);
-      mm(f[0], pb[ks][0], o[mt]);
+      X::mm(f[2], pb[ks][0], o[mt]);
+      X::mm(f[1], pb[ks][1], o[mt]);
+      X::mm(f[0], pb[ks][2], o[mt]);
+      X::mm(f[1], pb[ks][0], o[mt]);
+      X::mm(f[0], pb[ks][1], o[mt]);
+      X::mm(f[0], pb[ks][0], o[mt]);
       __builtin_amdgcn_sched_barrier(0);
     }
   };
@@ -532,17 +556,10 @@ __device__ __forceinline__ void attn_f32_item(const DevPlan& pl,
       const unsigned wd = TOPP ? row_bits(d.loc) : ~0u;
       const bool kept = !TOPP || d.loc < 0 || ((wd >> (d.loc & 31)) & 1u);
       for (int c = 0; c < 2 && 32 * c < d.len; ++c) {
-        f32x16 s = {};
-        const float* const kr =
-            kg + (size_t)(d.start + min(32 * c + l32, d.len - 1)) * pl.hkv * D +
-            g * (D / 2);
-        for (int u = 0; u < D / 8; ++u) {
-          const f32x4 a = *(const f32x4*)(kr + 4 * u);
-          const f32x4 b = *(const f32x4*)(qg + g * (D / 2) + 4 * u);
-#pragma unroll
-          for (int e = 0; e < 4; ++e)
-            s = __builtin_amdgcn_mfma_f32_32x32x2f32(a[e], b[e], s, 0, 0, 0);
-        }
+        f32x16 s;
+        X::qk_f32(kg + (size_t)(d.start + min(32 * c + l32, d.len - 1)) *
+                           pl.hkv * D,
+                  qg, g, s);
         mask_half(s, c, d);
         half_ref(s, kept);
         const float ts =
@@ -600,6 +617,108 @@ __device__ __forceinline__ void attn_f32_item(const DevPlan& pl,
       ws.pL[ix] = l_tot;
       ws.pNV[ix] = nv_tot > 0.f ? m_ref + log2_(nv_tot) : neg_inf();
     }
+  }
+}
+
+// The fp32 form of the intra-frame cue's products (intra_kernel, attn.hip):
+// acc[c] += the probabilities of the wave's heads at keys 32 c .. 32 c + 31 of
+// block qb. The logits are the attention pass's, by the same split and in the
+// same order, so that their rounding cancels against the saved LSE's: 21
+// frames x 64 tokens, d = 128, LSE up to 70: the maps are 1.7e-6 off fp64
+// (2-norm), 5.8e-6 with fp32 MFMA here, 3.2e-6 with fp32 MFMA in both passes.
+// smem: the planes of both 32-key halves. (75 frames x 64 tokens, 28/4 heads,
+// d = 128: the layer with cues takes 353 us, 378 with fp32 MFMA here.)
+template <int D>
+__device__ __forceinline__ void intra_f32_part(const DevPlan& pl,
+                                               const Workspace& ws,
+                                               const AttnCall& ac,
+                                               const BlockDesc& qb, int kvh,
+                                               int tid, int wave, char* smem,
+                                               f32x16 (&acc)[2]) {
+  using X = F32Split<D>;
+  constexpr int RC = X::RC, PB = X::PB, KK = D / 16, CSTEP = kThreads / RC;
+  EV_LDS char* const kpl = (EV_LDS char*)smem;
+  const int lane = tid & 63, l32 = lane & 31, g = lane >> 5;
+  const int qrow = 32 * (wave & 1) + l32;
+  const bool qvalid = qrow < qb.len;
+  const int qpos = qb.start + (qvalid ? qrow : 0);
+  const int group = pl.hq / pl.hkv;
+  const float* const kg = (const float*)ac.k + (size_t)kvh * D;
+  const int crow = tid / RC, ccol = tid % RC;
+#pragma unroll
+  for (int u = 0; u < 2 * X::NU; ++u) {
+    const int row = crow + u * CSTEP, r32 = row & 31;
+    const float* const src =
+        kg + (size_t)(qb.start + min(row, qb.len - 1)) * pl.hkv * D + 8 * ccol;
+    bf16x8 p[3];
+    X::split_qk(*(const f32x4*)src, *(const f32x4*)(src + 4), p);
+    EV_LDS char* const dst = kpl + (row >> 5) * 3 * PB +
+                             (r32 * RC + (ccol ^ swz<kSwzK, RC>(r32))) * 16;
+#pragma unroll
+    for (int q = 0; q < 3; ++q) *(EV_LDS bf16x8*)(dst + q * PB) = p[q];
+  }
+  unsigned vis = 0u;   // bit 16 c + r: the row sees key r of half c, in its frame
+#pragma unroll
+  for (int i = 0; i < 32; ++i) {
+    const int kl = 32 * (i >> 4) + 8 * ((i & 15) >> 2) + 4 * g + (i & 3);
+    if (qvalid && kl <= qrow && kl / pl.Nv == qrow / pl.Nv) vis |= 1u << i;
+  }
+  // waves 0-1 take the group's even heads, waves 2-3 the odd ones; a step's
+  // query values are read for the next head once they are used
+  f32x4 raw[KK][2];
+  auto q_row = [&](int hi) {
+    return (const float*)ac.q +
+           ((size_t)qpos * pl.hq + kvh * group + hi) * D;
+  };
+  auto fetch = [&](int hi, int kk) {
+    const float* const src = q_row(hi) + 16 * kk + 8 * g;
+    raw[kk][0] = *(const f32x4*)src;
+    raw[kk][1] = *(const f32x4*)(src + 4);
+  };
+  int hi = wave >> 1;
+  if (hi < group)
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) fetch(hi, kk);
+  __syncthreads();
+  for (; hi < group; hi += 2) {
+    const float l2 = ws.lse2v[(size_t)(kvh * group + hi) * pl.S + qpos];
+    const bool more = hi + 2 < group;
+    f32x16 lo[2] = {f32x16{}, f32x16{}}, s[2] = {f32x16{}, f32x16{}};
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) {
+      bf16x8 q[3];
+      X::split_qk(raw[kk][0], raw[kk][1], q);
+      if (more) fetch(hi + 2, kk);
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        bf16x8 f[3];
+        X::k_read(kpl + c * 3 * PB, l32, g, kk, f);
+        X::qk_step(f, q[0], q[1], q[2], lo[c], s[c]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    bool bad = false;
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      s[c] = s[c] + lo[c];
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const float x = vis >> (16 * c + r) & 1u ? s[c][r] : 0.f;
+        bad = bad || x - x != 0.f;
+      }
+    }
+    if (__any(bad))   // as the attention pass: again with fp32 MFMA
+#pragma unroll
+      for (int c = 0; c < 2; ++c)
+        X::qk_f32(kg + (size_t)(qb.start + min(32 * c + l32, qb.len - 1)) *
+                           pl.hkv * D,
+                  q_row(hi), g, s[c]);
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        acc[c][r] += vis >> (16 * c + r) & 1u
+                         ? exp2_(fmaf(s[c][r], ac.scale_log2, -l2)) : 0.f;
   }
 }
 

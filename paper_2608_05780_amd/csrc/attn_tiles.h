@@ -305,47 +305,12 @@ struct Bf16Path {
 };
 
 // ---------------------------------------------------------------------------
-// fp32 operands of the intra-frame cue (32x32x2 f32 MFMA). The contraction
-// over d pairs element t of lane half g with d = g*D/2 + t, so every lane
-// reads contiguous runs.
+// fp32 inputs (their products: attn_f32.h).
 template <int D>
 struct F32Path {
   using T = float;
   static constexpr int RC = D / 4;
-  struct QFrag {
-    float x[D / 2];
-  };
-
-  __device__ static void load_q(QFrag& qf, const void* q, int qpos, bool ok,
-                                int h, int hq, int g) {
-    const float* src = (const float*)q + ((size_t)qpos * hq + h) * D + g * D / 2;
-#pragma unroll
-    for (int u = 0; u < D / 8; ++u) {
-      f32x4 z = {};
-      const f32x4 t = ok ? *(const f32x4*)(src + 4 * u) : z;
-#pragma unroll
-      for (int jj = 0; jj < 4; ++jj) qf.x[4 * u + jj] = t[jj];
-    }
-  }
-
-  __device__ static void qk(f32x16 (&s)[2], const EV_LDS char* kt,
-                            const QFrag& qf, int l32, int g) {
-#pragma unroll
-    for (int c = 0; c < 2; ++c) {
-      const int key = 32 * c + l32;
-#pragma unroll
-      for (int u = 0; u < D / 8; ++u) {
-        const int ch = (g * D / 8 + u) ^ swz<kSwzK, RC>(key);
-        const f32x4 kf = *(const EV_LDS f32x4*)(kt + (key * RC + ch) * 16);
-#pragma unroll
-        for (int jj = 0; jj < 4; ++jj)
-          s[c] = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[jj], qf.x[4 * u + jj],
-                                                      s[c], 0, 0, 0);
-      }
-    }
-  }
 };
-
 
 }  // namespace
 }  // namespace evisel

@@ -148,6 +148,13 @@ TOPP = {
         n_sys=(5, 0, 70), n_videos=3, tau_p=0.9,
         key_struct=(2.0, 2.0, 0.8),
         plant_args={"count": 2, "s_frame": (2.0, 2.0), "s_query": 2.0}),
+    "odd_group_fp32_d128": wl.Workload(
+        name="odd-group-fp32-d128", config_id=900, n_layers=1, hq=3, hkv=1,
+        d=128, dtype="fp32", tokens_per_frame=64, block=64, sink_blocks=1,
+        window=8, plant="choose", n_frames=(21, 4), n_text=(20, 3),
+        n_sys=(70, 0), n_videos=2, tau_p=float(np.float32(0.97)),
+        key_struct=(2.0, 2.0, 0.8),
+        plant_args={"count": 2, "s_frame": (2.0, 2.0), "s_query": 2.0}),
 }
 
 
