@@ -221,6 +221,10 @@ SMALL = {
         "odd-group-fp32", dtype="fp32", d=64, hq=3, hkv=1,
         tokens_per_frame=16, n_frames=(48,), n_text=(100,), n_sys=(3,),
         key_struct=(2.0, 2.0, 0.8), tau_p=TAU),
+    "odd_group_fp32_d128": _small(
+        "odd-group-fp32-d128", dtype="fp32", hq=3, hkv=1, n_frames=(31, 4),
+        n_text=(100, 3), n_sys=(70, 0), n_videos=2,
+        key_struct=(2.0, 2.0, 0.8), tau_p=TAU),
 }
 
 

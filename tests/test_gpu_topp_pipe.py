@@ -2,11 +2,13 @@
 the same call when frame cues are requested): frames of every length, paired
 heads, short tails, query rows cut into chunks some of whose rows keep none of
 the chunk's tiles, and logits that rise or fall far beyond a row's first
-tile's (the pipelined kernel's recomputation)."""
+tile's (the pipelined kernel's recomputation). The same inputs go through the
+pipelined kernel against the oracle too."""
 import pytest
 
 import workloads as wl
 from gpu_harness import to_device
+from test_gpu_topp import _run_case, _scale_queries
 
 pytestmark = pytest.mark.gpu
 
@@ -67,3 +69,10 @@ def test_pipelined_matches_plain(name):
     rows = max(int(x) for x in nt)
     assert (ea - eb).abs().max() <= 1e-5 * rows
     assert (ta - tb).abs().max() <= 1e-5 * rows
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_pipelined_matches_oracle(name):
+    w, scale = CASES[name]
+    _run_case(w, transform=None if scale == 1.0 else
+              lambda x, lay, blk: _scale_queries(x, lay, blk, scale))
