@@ -208,6 +208,74 @@ def _check_work(m, csr, hq):
     assert all(len(x) == 1 for x in groups.values()), groups
 
 
+# (frames, query tokens, system tokens, N_v, hq, hkv, window) -> key blocks per
+# chunk of a query-token row, at most: the work's mean load per slot, or 16
+# where that is less, or where the longest row that is not split is shorter
+# still, that row's length (4 at least).
+CHUNKS = {
+    "window": (((12,), (64,), (0,), 64, 4, 1, 4), 6),
+    "sink_only": (((30,), (64,), (0,), 64, 2, 1, 0), 4),
+    "all_causal": (((10,), (64,), (0,), 64, 4, 1, -1), 10),
+    "long_rows": (((40,), (64,), (0,), 64, 2, 1, -1), 16),
+    "system_rows": (((5,), (64,), (700,), 64, 2, 1, 0), 13),
+    "mean_load": (((128,), (64,), (0,), 64, 12, 2, 4), 12),
+    "past_16": (((256,), (128,), (0,), 64, 28, 4, 8), 103),
+    # chunks of 12 would take the workspace (d = 128, with the frame cues)
+    # past the static one: chunks of 16 as in larger masks
+    "past_static": (((25,), (1406,), (0,), 8, 32, 1, -1), 16),
+}
+
+
+@pytest.mark.parametrize("name", list(CHUNKS))
+def test_query_row_chunks(lib, name):
+    (nf, nt, ns, nv, hq, hkv, window), want = CHUNKS[name]
+    m = _plan(nf, nt, nv, Rule(64, 1, window), hq=hq, hkv=hkv, n_sys=ns)
+    csr = ev.mask_export(m)
+    length = np.diff(csr["row_ptr"])
+    txt = csr["region"] == 2
+    load = -(-int((length + 1).sum()) * hkv * -(-(hq // hkv) // 2) // 512)
+    short = max(min(16, max(4, int(length[~txt].max()))), load)
+    slots = lambda c: hq * int((-(-length[txt] // c)).sum())
+    if name == "past_static":
+        # 64 query rows' O and three floats each, and the rest
+        more = (slots(short) - m.stats["n_chunk_slots"]) * 64 * (128 + 3) * 4
+        ws = ev.sparse_prefill_workspace(m, 128, cues=True)
+        assert short < 16
+        assert ws <= ev.NOALLOC_WORKSPACE_BYTES < ws + more
+    else:
+        assert short == want
+    assert m.stats["n_chunk_slots"] == slots(want)
+    _check_work(m, csr, hq)
+
+
+@pytest.mark.parametrize("tau_p", [0.0, 0.9])
+@pytest.mark.parametrize("hq,hkv", [(3, 1), (4, 2), (6, 3), (28, 4), (10, 5),
+                                    (8, 8), (12, 12), (16, 16)])
+def test_all_causal_items_are_dealt_evenly(lib, hq, hkv, tau_p):
+    """All-causal masks: the visual and system items go to the queues (one per
+    XCD, launch position mod 8) of their kv head where the kv heads divide the
+    queues, to all of them otherwise, and the queues they go to end within one
+    item of each other."""
+    m = _plan((70, 33), (40, 9), 64, Rule(64, 1, -1), hq=hq, hkv=hkv,
+              n_sys=(100, 0), tau_p=tau_p)
+    csr = ev.mask_export(m)
+    _check_work(m, csr, hq)
+    wk = ev.mask_export_work(m)
+    load, longest = np.zeros(8), 0
+    per = 8 // hkv if 8 % hkv == 0 else 8
+    for i, (qb, h, a, e) in enumerate(zip(wk["qblock"], wk["head"],
+                                          wk["kb_begin"], wk["kb_end"])):
+        if qb < 0:
+            continue
+        load[i % 8] += e - a + 1
+        if csr["region"][qb] != 2:
+            longest = max(longest, e - a + 1)
+            if per < 8:
+                assert i % 8 // per == h // (hq // hkv)
+    for x in range(0, 8, per):
+        assert np.ptp(load[x:x + per]) <= longest, load
+
+
 @pytest.mark.parametrize("ci", range(len(CASES)))
 def test_topp_plan_is_all_causal_candidates(lib, ci):
     """Top-p masks take every causal block as a candidate (the retained
