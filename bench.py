@@ -43,8 +43,8 @@ PEAK_HBM_GBS = 8000.0
 # Sources whose change invalidates the committed counter figures: the
 # attention kernel and the plan that orders its work (launch order decides
 # how much of the key/value traffic each XCD's L2 absorbs).
-TRAFFIC_SOURCES = ("attn.hip", "attn_pipe.hip", "attn_tiles.h", "plan.cpp",
-                   "plan.h")
+TRAFFIC_SOURCES = ("attn.hip", "attn_f32.h", "attn_pipe.hip", "attn_tiles.h",
+                   "plan.cpp", "plan.h")
 
 
 def traffic_source_sha():
@@ -201,39 +201,42 @@ def cue_record(w, st, S, T, prof):
 
 
 def coarse_work(ev, mask, w):
-    """Algorithmic work of one layer of coarse evidence: the block
-    affinities of every row against its history (MFMA on the mean keys'
-    bf16 hi and lo parts), the exact logits of its own block's causal prefix
-    and the video's system prefix (MFMA), and the bytes it must move at least
-    (Q read by the retention and by the coarse pass, K read by the mean-key
-    pooling, the evidence row written)."""
+    """Algorithmic work of one layer of coarse evidence: of the query rows, the
+    block affinities against their history (MFMA on the mean keys' bf16 hi and
+    lo parts) and the exact logits of their own block's causal prefix and the
+    video's system prefix (MFMA); and the bytes it must move at least (K read
+    by the mean-key pooling, the query rows' Q, the evidence row written)."""
     import numpy as np
     ex = ev.mask_export(mask)
-    flop = 0.0
+    flop, query_rows = 0.0, 0
     parts = 2 if w.dtype == "bf16" else 1
     for n in np.unique(ex["video"]):
         ids = np.nonzero(ex["video"] == n)[0]
         sys_len = int(ex["len"][ids][ex["region"][ids] == 0].sum())
         sel = ids[ex["region"][ids] != 0]
         for i, b in enumerate(sel):
+            if ex["region"][b] != 2:
+                continue
             rows = int(ex["len"][b])
+            query_rows += rows
             # history: the selectable blocks before b; exact part: the
             # system prefix and the causal prefix of b (rows x (rows+1)/2)
             flop += 2.0 * w.d * w.hq * (parts * rows * i + rows * sys_len +
                                         rows * (rows + 1) / 2)
     esz = 2 if w.dtype == "bf16" else 4
     S, T = mask.stats["n_tokens"], mask.stats["n_frames_total"]
-    nbytes = (2 * S * w.hq * w.d * esz + S * w.hkv * w.d * esz +
+    nbytes = (query_rows * w.hq * w.d * esz + S * w.hkv * w.d * esz +
               w.hq * T * 4)
     return flop, nbytes
 
 
 def coarse_main(args, ev, w, mask, qs, kks, evid, e_qf, kk, topk, ws,
                 stream, S, T, L, ks, core):
-    """--coarse: the paper's coarse query-frame evidence of every layer
-    (the retention kernels plus the coarse pass), then the frame
-    aggregation and top-k; timed like the exact probe, with HIP events
-    around every layer's coarse call on the caller's stream."""
+    """--coarse: the paper's coarse query-frame evidence of every layer (mean
+    keys, the coarse pass, which decides the query rows' retention itself, and
+    its reduction), then the frame aggregation and top-k; timed like the exact
+    probe, with HIP events around every layer's coarse call on the caller's
+    stream."""
     import numpy as np
     import torch
 
@@ -262,8 +265,8 @@ def coarse_main(args, ev, w, mask, qs, kks, evid, e_qf, kk, topk, ws,
     step(evs)
     torch.cuda.synchronize()
     layer_ms = float(np.mean([a.elapsed_time(b) for a, b in evs]))
-    # the retention alone (mean keys + per-row selection) per layer, from
-    # one further pass of evisel_select_blocks calls, each bracketed
+    # beside it, and no part of it: every row's retention (mean keys and
+    # per-row selection, evisel_select_blocks), each call bracketed
     st = mask.stats
     rb = torch.empty((w.hq, st["n_blocks"], st["hist_words"], 64),
                      dtype=torch.int32, device="cuda")
@@ -279,8 +282,8 @@ def coarse_main(args, ev, w, mask, qs, kks, evid, e_qf, kk, topk, ws,
     flop, nbytes = coarse_work(ev, mask, w)
     found = sorted(topk[:sum(ks)].cpu().numpy().tolist())
     rec = {
-        "metric": "coarse-evidence probe tokens/sec (top-p retention + "
-                  "coarse query-frame evidence)",
+        "metric": "coarse-evidence probe tokens/sec (coarse query-frame "
+                  "evidence under top-p retention)",
         "value": S / (ms_step * 1e-3),
         "unit": "tokens/s",
         "n_gpus": 1,
@@ -298,7 +301,7 @@ def coarse_main(args, ev, w, mask, qs, kks, evid, e_qf, kk, topk, ws,
                    "block": w.block, "tau_p": w.tau_p,
                    "parallelism": "single-gpu"},
         "coarse": {"ms_per_layer": layer_ms,
-                   "retention_ms_per_layer": sel_ms,
+                   "select_blocks_ms_per_layer": sel_ms,
                    "algorithmic_flop_per_layer": flop,
                    "algorithmic_bytes_per_layer": nbytes,
                    "achieved_TFLOPs": flop / (layer_ms * 1e-3) / 1e12,
