@@ -110,10 +110,12 @@ evisel_status make_plan(const evisel_layout* layout,
   std::string err;
   try {
     err = evisel::build_plan(L, R, hq, hkv, &m->plan);
-    // short chunks must not take a mask past the static workspace
+    // short chunks are for lists that start at once, and must not take a mask
+    // past the static workspace
     if (err.empty() && m->plan.chunk_blocks < evisel::kChunkBlocks) {
       const WsLayout w = ws_layout(m->plan, 128);
-      if (w.total + w.cue_total > EVISEL_NOALLOC_WORKSPACE_BYTES)
+      if (m->plan.longest_queue > evisel::kQueueSlots ||
+          w.total + w.cue_total > EVISEL_NOALLOC_WORKSPACE_BYTES)
         err = evisel::build_plan(L, R, hq, hkv, &m->plan, false);
     }
   } catch (const std::bad_alloc&) {

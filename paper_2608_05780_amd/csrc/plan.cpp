@@ -199,17 +199,40 @@ std::string build_plan(const Layout& L, const Rule& R, int32_t hq, int32_t hkv,
     total += (int64_t)(P.row_ptr[b + 1] - P.row_ptr[b] + 1) * hkv * pairs;
   const int64_t avg = (total + kTargetSlots - 1) / kTargetSlots;
   // Query-token rows are split into chunks of the mean load, but of 16 key
-  // blocks at least (each chunk leaves a partial). Where the mean load is
-  // below that, the chip is mostly idle and the longest item sets the time:
-  // there the chunks go down to the longest row that is not split (shorter
-  // ones would only add partials). Three clips of 16-token frames, 12 / 2
-  // heads, d = 64, rows of 7 tiles: 30.3 us with chunks of 12, 23.9 with 7;
-  // 32 fp32 frames, all-causal rows of 8: 51.8 us with 9, 45.1 with 8 at most.
+  // blocks at least (each chunk leaves a partial). Where the whole list is on
+  // the chip at once, the longest item sets the time: there the chunks go down
+  // to the longest row that is not split (shorter ones would only add
+  // partials). Three clips of 16-token frames, 12 / 2 heads, d = 64, rows of 7
+  // tiles: 29.1 us with chunks of 12, 22.3 with 7; 32 fp32 frames, all-causal
+  // rows of 8: 51.8 us with 9, 45.1 with 8 at most. A list that some queue
+  // cannot start at once only gets longer (64 tokens per frame, d = 128, rows of
+  // 6 tiles: 80 frames, 12 / 2 heads, 130 query tokens 36.4 us with chunks of
+  // 16, 40.5 with 8; 32 frames, 28 / 4 heads, 64 query tokens 28.6 and 32.1):
+  // more items than slots keep 16, and so do plans whose longest queue turns out
+  // to exceed its share (make_plan).
   int32_t longest = short_chunks ? 4 : kChunkBlocks;
   for (int32_t b = 0; b < nb; ++b)
     if (P.blocks[b].region != kTxt)
       longest = std::max(longest, P.row_ptr[b + 1] - P.row_ptr[b]);
   P.chunk_blocks = (int32_t)std::max<int64_t>(std::min(kChunkBlocks, longest), avg);
+  if (P.chunk_blocks < kChunkBlocks) {
+    int64_t items = 0;   // of one kv head: head pairs, and the odd head's
+    auto count = [&](int64_t n, int64_t paired_n) {
+      items += n * (group / kHeadsPerItem) + paired_n * (group % kHeadsPerItem);
+    };
+    for (size_t n = 0; n < nseq; ++n) {
+      for (int64_t m : {sysb[n].size(), visb[n].size()}) count(m, (m + 1) / 2);
+      for (size_t t = 0; t < txtb[n].size(); ++t) {
+        const int32_t b = txtb[n][t];
+        const int64_t nch =
+            (P.row_ptr[b + 1] - P.row_ptr[b] + P.chunk_blocks - 1) /
+            P.chunk_blocks;
+        // (of a pair of tiles the second has no fewer chunks)
+        count(nch, t % 2 == 1 || t + 1 == txtb[n].size() ? nch : 0);
+      }
+    }
+    if (items * hkv > kXcds * kQueueSlots) P.chunk_blocks = kChunkBlocks;
+  }
 
   // Paired items: the kv group's odd head takes two query blocks in one
   // item. Both CSR rows are in ascending key-block order, so their runs
@@ -399,6 +422,7 @@ std::string build_plan(const Layout& L, const Rule& R, int32_t hq, int32_t hkv,
   }
   size_t rounds = 0;
   for (auto& v : q) rounds = std::max(rounds, v.size());
+  P.longest_queue = (int32_t)rounds;
   P.items.reserve(rounds * kXcds);
   for (size_t r = 0; r < rounds; ++r)
     for (int x = 0; x < kXcds; ++x) {

@@ -119,6 +119,7 @@ struct Plan {
   // sizes
   int64_t S = 0, T = 0, n_text_rows = 0, segtot = 0, n_slots = 0;
   int32_t chunk_blocks = 0;   // max key blocks per split item
+  int32_t longest_queue = 0;  // items of the fullest hardware queue
   // tables
   std::vector<BlockDesc> blocks;
   std::vector<int32_t> row_ptr, col;
@@ -152,7 +153,9 @@ std::string build_plan(const Layout& layout, const Rule& rule, int32_t hq,
 constexpr int kXcds = 8;
 // Key blocks a chunk of a split query-token row holds at least (larger masks).
 constexpr int kChunkBlocks = 16;
-// Concurrent work items the split heuristic aims to fill (256 CUs x 1).
+// Concurrent work items the split heuristic aims to fill (256 CUs x 2), and
+// those of one queue's 32 CUs.
 constexpr int kTargetSlots = 512;
+constexpr int kQueueSlots = kTargetSlots / kXcds;
 
 }  // namespace evisel

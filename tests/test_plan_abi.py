@@ -210,19 +210,24 @@ def _check_work(m, csr, hq):
 
 # (frames, query tokens, system tokens, N_v, hq, hkv, window) -> key blocks per
 # chunk of a query-token row, at most: the work's mean load per slot, or 16
-# where that is less, or where the longest row that is not split is shorter
-# still, that row's length (4 at least).
+# where that is less; or, where the longest row that is not split is shorter
+# still and every queue then holds 64 items at most, that row's length (4 at
+# least).
 CHUNKS = {
     "window": (((12,), (64,), (0,), 64, 4, 1, 4), 6),
     "sink_only": (((30,), (64,), (0,), 64, 2, 1, 0), 4),
     "all_causal": (((10,), (64,), (0,), 64, 4, 1, -1), 10),
     "long_rows": (((40,), (64,), (0,), 64, 2, 1, -1), 16),
     "system_rows": (((5,), (64,), (700,), 64, 2, 1, 0), 13),
-    "mean_load": (((128,), (64,), (0,), 64, 12, 2, 4), 12),
+    "odd_heads": (((24,), (130,), (0,), 64, 28, 4, 8), 10),
     "past_16": (((256,), (128,), (0,), 64, 28, 4, 8), 103),
-    # chunks of 12 would take the workspace (d = 128, with the frame cues)
-    # past the static one: chunks of 16 as in larger masks
-    "past_static": (((25,), (1406,), (0,), 8, 32, 1, -1), 16),
+    # the slots hold the list: 444 items, 59 in the longest queue
+    "all_start": (((60,), (64,), (0,), 64, 12, 2, 8), 10),
+    # 486 items with chunks of 10, but 70 in one queue
+    "long_queue": (((60,), (130,), (0,), 64, 12, 2, 8), 16),
+    # 546 items with chunks of 8
+    "many_items": (((80,), (64,), (0,), 64, 12, 2, 4), 16),
+    "many_items_odd": (((32,), (64,), (0,), 64, 28, 4, 4), 16),
 }
 
 
@@ -234,17 +239,14 @@ def test_query_row_chunks(lib, name):
     length = np.diff(csr["row_ptr"])
     txt = csr["region"] == 2
     load = -(-int((length + 1).sum()) * hkv * -(-(hq // hkv) // 2) // 512)
-    short = max(min(16, max(4, int(length[~txt].max()))), load)
     slots = lambda c: hq * int((-(-length[txt] // c)).sum())
-    if name == "past_static":
-        # 64 query rows' O and three floats each, and the rest
-        more = (slots(short) - m.stats["n_chunk_slots"]) * 64 * (128 + 3) * 4
-        ws = ev.sparse_prefill_workspace(m, 128, cues=True)
-        assert short < 16
-        assert ws <= ev.NOALLOC_WORKSPACE_BYTES < ws + more
-    else:
-        assert short == want
     assert m.stats["n_chunk_slots"] == slots(want)
+    wk = ev.mask_export_work(m)
+    queue = max(int((wk["qblock"][x::8] >= 0).sum()) for x in range(8))
+    if want < 16:
+        assert want == max(4, int(length[~txt].max()), load) and queue <= 64
+    else:
+        assert want == max(16, load)
     _check_work(m, csr, hq)
 
 
