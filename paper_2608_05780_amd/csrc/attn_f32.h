@@ -4,10 +4,9 @@
 //
 // The fp32 MFMA runs at 1/16 of the bf16 rate, and both products of a tile on
 // it bound the fp32 kernel (83 TFLOP/s of the 153 a large fp32 product
-// reaches; 541 us a layer of 75 frames x 64 tokens, 28/4 heads, d = 128; now
-// 306 us, and the output's relative error against fp64 5.0e-7, now 3.4e-7).
-// Here every
-// fp32 operand is the exact sum of three bf16 values, x = h + m + l with
+// reaches; 537 us a layer of 75 frames x 64 tokens, 28/4 heads, d = 128; now
+// 305 us, and the output's relative error against fp64 5.0e-7, now 3.3e-7).
+// Here every fp32 operand is the exact sum of three bf16 values, x = h + m + l with
 // h = RNE(x), m = RNE(x - h), l = x - h - m (8 + 8 + 8 significant bits), and
 // a product is the six partial products down to 2^-17 of it, each exact in
 // the fp32 accumulator: h h, h m, m h, m m, h l, l h. What is left out, m l,
@@ -31,7 +30,9 @@
 // swizzle) and V (transposed-read swizzle); the next half's loads are issued
 // right after, so they run beside the MFMAs. Planes and raw rows are 80 KB at
 // d = 128: two work-groups share a CU, and one splits (VALU, LDS writes)
-// while the other multiplies.
+// while the other multiplies. (The top-p form's tile list takes it to 84 KB
+// there: one work-group a CU, without that overlap. 75 frames, retention and
+// all: 1,278 us, 1,823 with fp32 MFMA, whose 128 KB held one as well.)
 #pragma once
 #include <type_traits>
 

@@ -598,7 +598,7 @@ __device__ __forceinline__ void frame_pair(const DevPlan& pl,
 }
 
 // The frame cues' last step, one launch (256 frames x 64 tokens, 28/4 heads: the
-// layer takes 254.7 us, 262.1 with two launches): work-groups [0, n_pair_blocks) take
+// layer takes 259 us, 261 with two launches): work-groups [0, n_pair_blocks) take
 // the cross-frame pairs, the others the intra-frame maps, whose partial sums
 // per kv head (intra_kernel) are added in kv head order and divided by Hq.
 constexpr int kReduceVec = 4;   // map entries per thread (N_v^2 is a multiple)
