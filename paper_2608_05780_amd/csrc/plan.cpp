@@ -203,7 +203,7 @@ std::string build_plan(const Layout& L, const Rule& R, int32_t hq, int32_t hkv,
   // the chip at once, the longest item sets the time: there the chunks go down
   // to the longest row that is not split (shorter ones would only add
   // partials). Three clips of 16-token frames, 12 / 2 heads, d = 64, rows of 7
-  // tiles: 29.1 us with chunks of 12, 22.3 with 7; 32 fp32 frames, all-causal
+  // tiles: 28.0 us with chunks of 16, 21.4 with 7; 32 fp32 frames, all-causal
   // rows of 8: 51.8 us with 9, 45.1 with 8 at most. A list that some queue
   // cannot start at once only gets longer (64 tokens per frame, d = 128, rows of
   // 6 tiles: 80 frames, 12 / 2 heads, 130 query tokens 36.4 us with chunks of
