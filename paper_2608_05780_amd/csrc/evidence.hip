@@ -54,16 +54,41 @@ __device__ __forceinline__ float log2_(float x) {
 
 // Chunks are taken kChunkGroup at a time, their loads in flight together (past
 // the last chunk: its own again, not counted); one at a time each waited for
-// its own round trip, about 1.4 us a chunk over the two loops below. One code
-// path for all counts: groups of 8, 4, 2 and 1 take less time from 8 chunks on,
+// its own round trip, about 1.4 us a chunk over the two passes below (references,
+// then sums; up to four chunks need one round trip for both). One code path
+// for all counts: groups of 8, 4, 2 and 1 take less time from 8 chunks on,
 // but the longer code 0.7 us more on three.
 constexpr int kChunkGroup = 4;
 
-// Largest reference of row r over chunk slots slot0 .. slot0 + nch - 1.
+// References and row sums of row r in chunk slots slot0 + c .. (nch in all).
+struct ChunkRefs {
+  float m[kChunkGroup], l[kChunkGroup];
+  __device__ __forceinline__ void load(const Workspace& ws, int slot0, int nch,
+                                       int c, int r) {
+#pragma unroll
+    for (int u = 0; u < kChunkGroup; ++u) {
+      const size_t ix = (size_t)(slot0 + min(c + u, nch - 1)) * kTile + r;
+      m[u] = ws.pM[ix];
+      l[u] = ws.pL[ix];
+    }
+  }
+  __device__ __forceinline__ float most() const {
+    float M = neg_inf();
+#pragma unroll
+    for (int u = 0; u < kChunkGroup; ++u) M = fmaxf(M, m[u]);
+    return M;
+  }
+  // weight of chunk u in a row of reference M
+  __device__ __forceinline__ float weight(int u, float M) const {
+    return m[u] == neg_inf() ? 0.f : exp2_(m[u] - M);
+  }
+};
+
+// Largest reference of row r over all chunks, those of the first group in g.
 __device__ __forceinline__ float row_ref(const Workspace& ws, int slot0,
-                                         int nch, int r) {
-  float M = neg_inf();
-  for (int c = 0; c < nch; c += kChunkGroup) {
+                                         int nch, int r, const ChunkRefs& g) {
+  float M = g.most();
+  for (int c = kChunkGroup; c < nch; c += kChunkGroup) {
     float m[kChunkGroup];
 #pragma unroll
     for (int u = 0; u < kChunkGroup; ++u)
@@ -74,28 +99,20 @@ __device__ __forceinline__ float row_ref(const Workspace& ws, int slot0,
   return M;
 }
 
-// Weight of a chunk of reference m in a row of reference M.
-__device__ __forceinline__ float chunk_weight(float m, float M) {
-  return m == neg_inf() ? 0.f : exp2_(m - M);
-}
-
 // log2 LSE of row r of a query-token tile from its chunk partials (chunk
-// slots slot0 .. slot0 + nch - 1).
+// slots slot0 .. slot0 + nch - 1; at least one).
 __device__ __forceinline__ float row_lse2(const Workspace& ws, int slot0,
                                           int nch, int r) {
-  const float M = row_ref(ws, slot0, nch, r);
+  ChunkRefs g;
+  g.load(ws, slot0, nch, 0, r);
+  const float M = row_ref(ws, slot0, nch, r, g);
   float L = 0.f;
-  for (int c = 0; c < nch; c += kChunkGroup) {
-    float m[kChunkGroup], l[kChunkGroup];
-#pragma unroll
-    for (int u = 0; u < kChunkGroup; ++u) {
-      const size_t ix = (size_t)(slot0 + min(c + u, nch - 1)) * kTile + r;
-      m[u] = ws.pM[ix];
-      l[u] = ws.pL[ix];
-    }
+  for (int c = 0;;) {
 #pragma unroll
     for (int u = 0; u < kChunkGroup; ++u)
-      if (c + u < nch) L += chunk_weight(m[u], M) * l[u];
+      if (c + u < nch) L += g.weight(u, M) * g.l[u];
+    if ((c += kChunkGroup) >= nch) break;
+    g.load(ws, slot0, nch, c, r);
   }
   return M + log2_(L);
 }
@@ -142,32 +159,35 @@ __global__ __launch_bounds__(kCeThreads) void combine_evidence_kernel(
     const int r = tid >> 4, part = tid & 15;
     if (r >= qb.len) return;
     const int slot0 = tt.slot0 + h * tt.n_chunks;
-    const float M = row_ref(ws, slot0, tt.n_chunks, r);
+    ChunkRefs g;
+    f32x4 t[kChunkGroup][DP / 4];
+    auto load = [&](int c) {
+      g.load(ws, slot0, tt.n_chunks, c, r);
+#pragma unroll
+      for (int u = 0; u < kChunkGroup; ++u) {
+        const int slot = slot0 + min(c + u, tt.n_chunks - 1);
+        const float* po = ws.pO + ((size_t)slot * kTile + r) * D + part * DP;
+#pragma unroll
+        for (int i = 0; i < DP / 4; ++i) t[u][i] = *(const f32x4*)(po + 4 * i);
+      }
+    };
+    load(0);
+    const float M = row_ref(ws, slot0, tt.n_chunks, r, g);
     float L = 0.f;
     float acc[DP];
 #pragma unroll
     for (int i = 0; i < DP; ++i) acc[i] = 0.f;
-    for (int c = 0; c < tt.n_chunks; c += kChunkGroup) {
-      float m[kChunkGroup], l[kChunkGroup];
-      f32x4 t[kChunkGroup][DP / 4];
-#pragma unroll
-      for (int u = 0; u < kChunkGroup; ++u) {
-        const size_t ix =
-            (size_t)(slot0 + min(c + u, tt.n_chunks - 1)) * kTile + r;
-        m[u] = ws.pM[ix];
-        l[u] = ws.pL[ix];
-        const float* po = ws.pO + ix * D + part * DP;
-#pragma unroll
-        for (int i = 0; i < DP / 4; ++i) t[u][i] = *(const f32x4*)(po + 4 * i);
-      }
+    for (int c = 0;;) {
 #pragma unroll
       for (int u = 0; u < kChunkGroup; ++u) {
         if (c + u >= tt.n_chunks) break;
-        const float w = chunk_weight(m[u], M);
-        L += w * l[u];
+        const float w = g.weight(u, M);
+        L += w * g.l[u];
 #pragma unroll
         for (int i = 0; i < DP; ++i) acc[i] += w * t[u][i / 4][i % 4];
       }
+      if ((c += kChunkGroup) >= tt.n_chunks) break;
+      load(c);
     }
     const float inv = 1.f / L;
     const int qpos = qb.start + r;
