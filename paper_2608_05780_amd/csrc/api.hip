@@ -225,6 +225,7 @@ evisel_status upload(evisel_mask* m, hipStream_t s) {
   for (int32_t loc : P.blk_local) hmax = std::max(hmax, loc);
   dp.hmax = hmax;
   dp.topp = P.rule.tau > 0.f ? 1 : 0;
+  dp.max_tiles = P.max_item_candidates;
   dp.max_frames = 0;
   for (const auto& sq : P.seqs)
     dp.max_frames = std::max(dp.max_frames, sq.n_frames);

@@ -810,10 +810,14 @@ attn_pipe_topp_kernel(const PipeArgs a) {
 
 bool attention_pipe_supported(const DevPlan& p, const AttnCall& c) {
   // frame cues: frames of 32 or 64 keys (the loop keeps two half-tile sums),
-  // and not with top-p (the two forms together run out of registers)
+  // and not with top-p (the two forms together run out of registers); top-p:
+  // not where every item ends before the pipeline fills (4 / 1 heads, d = 64,
+  // 8-token frames: items of up to 2 tiles 10.7 us, 11.4 here; of 4 tiles 30.4
+  // and 31.3 for the layer; from 5 on equal, then faster)
   const bool cues = c.segv != nullptr || c.lse2v != nullptr;
+  constexpr int kShortItem = 4;
   return !c.fp32 && (!cues || (p.Nv >= 32 && !p.topp)) &&
-         (c.d == 64 || c.d == 128);
+         !(p.topp && p.max_tiles <= kShortItem) && (c.d == 64 || c.d == 128);
 }
 
 hipError_t launch_attention_pipe(const DevPlan& p, const Workspace& w,

@@ -33,6 +33,7 @@ struct DevPlan {
   int32_t W;                 // history words per row (top-p)
   int32_t hmax;              // longest block history (top-p)
   int32_t topp;              // 1: adaptive top-p retention
+  int32_t max_tiles;         // key tiles of the longest work item
   int32_t max_frames;        // frames of the longest video
 };
 

@@ -221,6 +221,15 @@ SMALL = {
         "odd-group-fp32", dtype="fp32", d=64, hq=3, hkv=1,
         tokens_per_frame=16, n_frames=(48,), n_text=(100,), n_sys=(3,),
         key_struct=(2.0, 2.0, 0.8), tau_p=TAU),
+    # items of up to 2, 4 and 5 key tiles: the unpipelined kernel's last and
+    # the pipelined one's first
+    "two_tiles": _small("two-tiles", d=64, hq=4, hkv=1, tokens_per_frame=16,
+                        n_frames=(4,), n_text=(3,), n_sys=(0,)),
+    "four_tiles": _small("four-tiles", hq=3, hkv=1, tokens_per_frame=64,
+                         n_frames=(3,), n_text=(9,), n_sys=(0,)),
+    "five_tiles": _small("five-tiles", hq=3, hkv=1, tokens_per_frame=64,
+                         n_frames=(3, 2), n_text=(70, 5), n_sys=(0, 4),
+                         n_videos=2),
     "odd_group_fp32_d128": _small(
         "odd-group-fp32-d128", dtype="fp32", hq=3, hkv=1, n_frames=(31, 4),
         n_text=(100, 3), n_sys=(70, 0), n_videos=2,
